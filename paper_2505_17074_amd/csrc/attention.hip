@@ -33,15 +33,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float wave_max(float x) {
-  for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-  return x;
-}
-
 // Visibility of KV position t (relative to the request's first KV row) to a
 // query whose node has ancestor mask `anc`; ctx = cached positions.
 __device__ __forceinline__ bool visible(int t, int ctx, uint32_t anc) {
@@ -118,30 +109,41 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 #ifndef SV_NS_W5
 #define SV_NS_W5 3
 #endif
+// fp32 inputs: two stages (32 KB), so that four one-wave work-groups share a
+// compute unit; three stages run the wider builds within 3 %.
+#ifndef SV_NS_F32
+#define SV_NS_F32 2
+#endif
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4_t;
 
-template <int D>
+// T: uint16_t (bf16 inputs) or float (fp32 inputs)
+template <typename T, int D>
 struct Geo {
-  static constexpr int CH = D / 8;                  // 16-byte chunks per row
+  // keys per tile: a tile's K and V are 8 KB each (4 KB for bf16 at d = 64)
+  static constexpr int TK = sizeof(T) == 4 && D == 128 ? 16 : 32;
+  static constexpr int ROWB = D * (int)sizeof(T);   // bytes of one LDS row
+  static constexpr int CH = ROWB / 16;              // 16-byte chunks per row
   static constexpr int RPI = 64 / CH;               // rows per 1 KB transfer
-  static constexpr int IPM = 32 / RPI;              // transfers per 32-row matrix
-  static constexpr int ROWB = D * 2;                // bytes of one LDS row
-  static constexpr int MAT = 32 * ROWB;             // bytes of one K (or V) tile
+  static constexpr int IPM = TK / RPI;              // transfers per TK-row matrix
+  static constexpr int MAT = TK * ROWB;             // bytes of one K (or V) tile
   static constexpr int STAGE = 2 * MAT;
 };
 
 // K rows: distinct over the 16 rows of one quarter-wave A read.
-template <int D>
+template <typename T, int D>
 __device__ __forceinline__ int swk(int r) {
-  if constexpr (D == 128) return (r & 3) | (((r >> 3) & 3) << 2);
+  if constexpr (sizeof(T) == 4) return r & 15;
+  else if constexpr (D == 128) return (r & 3) | (((r >> 3) & 3) << 2);
   else return ((r >> 1) & 1) | (((r >> 3) & 3) << 1);
 }
 // V rows: even (keeps 32-byte column pairs together), distinct pair slots over
-// the 8 rows of one half-wave transpose read.
-template <int D>
+// the 8 rows of one half-wave transpose read.  fp32: a quarter-wave reads 256
+// contiguous bytes of one row, which needs no swizzle.
+template <typename T, int D>
 __device__ __forceinline__ int swv(int r) {
-  if constexpr (D == 128) return 2 * ((r & 3) | (((r >> 3) & 1) << 2));
+  if constexpr (sizeof(T) == 4) return 0;
+  else if constexpr (D == 128) return 2 * ((r & 3) | (((r >> 3) & 1) << 2));
   else return 2 * (((r >> 1) & 1) | (((r >> 3) & 1) << 1));
 }
 
@@ -174,9 +176,9 @@ __device__ __forceinline__ void ring_barrier() {
 // A tile's transfers are dealt round-robin over the waves: wave w issues
 // transfers w, w + W, ... < NI, PER of them when w < FULL, else PER - 1 (an
 // uneven split issues no padding transfer; each wave waits on its own count).
-template <int D, int W>
+template <typename T, int D, int W>
 struct Xfer {
-  static constexpr int NI = 2 * Geo<D>::IPM;        // transfers per tile (K then V)
+  static constexpr int NI = 2 * Geo<T, D>::IPM;        // transfers per tile (K then V)
   static constexpr int PER = (NI + W - 1) / W;      // per wave, at most
   static constexpr int FULL = NI - (PER - 1) * W;   // waves that issue PER
   static constexpr bool EVEN = NI % W == 0;         // every wave issues PER
@@ -184,37 +186,37 @@ struct Xfer {
 
 // Byte offset, inside a tile, of the global chunk lane `lane` moves in
 // transfer j (tile row row_in_tile * row_bytes + swizzled chunk).
-template <int D>
+template <typename T, int D>
 __device__ __forceinline__ uint32_t xfer_offset(int j, int lane, int row_bytes, int* row_in_tile) {
-  using G = Geo<D>;
+  using G = Geo<T, D>;
   const bool isv = j >= G::IPM;
   const int jj = isv ? j - G::IPM : j;
   const int row = jj * G::RPI + lane / G::CH;
-  const int chunk = (lane % G::CH) ^ (isv ? swv<D>(row) : swk<D>(row));
+  const int chunk = (lane % G::CH) ^ (isv ? swv<T, D>(row) : swk<T, D>(row));
   *row_in_tile = row;
   return (uint32_t)row * (uint32_t)row_bytes + (uint32_t)chunk * 16u;
 }
 
-template <int D, int W>
+template <typename T, int D, int W>
 struct XferPlan {
-  uint32_t off[Xfer<D, W>::PER];    // per-lane byte offset inside the tile
+  uint32_t off[Xfer<T, D, W>::PER];    // per-lane byte offset inside the tile
 };
 
 // Wave w's transfers of the tile starting at key t0 into `stage`, as
 // buffer_load_dwordx4 ... lds with the tile start in soffset and each lane's
 // precomputed offset in voffset.  Tiles that reach past ke clamp their rows
 // to ke - 1 (in bounds, masked later).
-template <int D, int W>
+template <typename T, int D, int W>
 __device__ __forceinline__ void issue_tile(char* stage, __amdgpu_buffer_rsrc_t rk, __amdgpu_buffer_rsrc_t rv,
                                            int row_bytes, int t0, int ke, int w, int lane,
-                                           const XferPlan<D, W>& X) {
-  using G = Geo<D>;
-  if (t0 + 32 <= ke) {                // wave-uniform: the whole tile is inside the item
+                                           const XferPlan<T, D, W>& X) {
+  using G = Geo<T, D>;
+  if (t0 + G::TK <= ke) {                // wave-uniform: the whole tile is inside the item
     const uint32_t soff = (uint32_t)t0 * (uint32_t)row_bytes;
 #pragma unroll
-    for (int q = 0; q < Xfer<D, W>::PER; ++q) {
-      if constexpr (!Xfer<D, W>::EVEN)
-        if (w + q * W >= Xfer<D, W>::NI) break;     // wave-uniform: this wave's last is done
+    for (int q = 0; q < Xfer<T, D, W>::PER; ++q) {
+      if constexpr (!Xfer<T, D, W>::EVEN)
+        if (w + q * W >= Xfer<T, D, W>::NI) break;     // wave-uniform: this wave's last is done
       const int j = w + q * W;
       const bool isv = j >= G::IPM;
       const int jj = isv ? j - G::IPM : j;
@@ -223,14 +225,14 @@ __device__ __forceinline__ void issue_tile(char* stage, __amdgpu_buffer_rsrc_t r
     }
   } else {
 #pragma unroll
-    for (int q = 0; q < Xfer<D, W>::PER; ++q) {
-      if constexpr (!Xfer<D, W>::EVEN)
-        if (w + q * W >= Xfer<D, W>::NI) break;     // wave-uniform: this wave's last is done
+    for (int q = 0; q < Xfer<T, D, W>::PER; ++q) {
+      if constexpr (!Xfer<T, D, W>::EVEN)
+        if (w + q * W >= Xfer<T, D, W>::NI) break;     // wave-uniform: this wave's last is done
       const int j = w + q * W;
       const bool isv = j >= G::IPM;
       const int jj = isv ? j - G::IPM : j;
       int row;
-      const uint32_t full = xfer_offset<D>(j, lane, row_bytes, &row);
+      const uint32_t full = xfer_offset<T, D>(j, lane, row_bytes, &row);
       const uint32_t chunk_bytes = full - (uint32_t)row * (uint32_t)row_bytes;
       const int key = min(t0 + row, ke - 1);       // >= kb >= 0: items are never empty
       __builtin_amdgcn_raw_ptr_buffer_load_lds(isv ? rv : rk, (lds_void_t*)(stage + (isv ? G::MAT : 0) + jj * 1024),
@@ -239,23 +241,124 @@ __device__ __forceinline__ void issue_tile(char* stage, __amdgpu_buffer_rsrc_t r
   }
 }
 
-template <int D>
+template <typename T, int D>
 struct RowTile {
-  bf16x8 q[D / 32];
+  static constexpr bool F32 = sizeof(T) == 4;
+  using QV = typename std::conditional<F32, f32x4, bf16x8>::type;
+  static constexpr int KS = Geo<T, D>::CH / 4;      // 16-byte query (and K) chunks per lane
+  QV q[KS];                // chunks 4 ks + lane group of the lane's query row
   f32x4 o[D / 16];
-  uint32_t koff[D / 32];   // A-row read offsets (key tile 0; tile 1 is +4 rows)
-  uint32_t voff[D / 16];   // transpose-read offsets (keys 8g + 0..3; +4 rows for 4..7)
+  uint32_t koff[KS];       // A-row read offsets (key tile 0; bf16 tile 1 is +4 rows, fp32 tile 1 +16)
+  uint32_t voff[F32 ? 1 : D / 16];   // bf16: transpose-read offsets (keys 8g + 0..3; +4 rows for 4..7)
   uint32_t anc;
   float m, l;
 };
+
+// Lazy softmax reference over this lane's N masked scores of one tile (log2
+// units).  The exponent reference m trails the running max by at most kLazy:
+// it moves (and O, l are rescaled) only when a score exceeds it by more than
+// that, so p <= 2^kLazy and the common tile leaves the accumulators to the
+// matrix cores alone.  Returns the reference to subtract (0 while every score
+// so far is masked).
+template <int N, int ET>
+__device__ __forceinline__ float lazy_reference(const float (&sv)[N], float& m, float& l, f32x4 (&o)[ET]) {
+  constexpr float kLazy = 8.f;
+  // this lane's largest score (a masked -inf never wins over a finite one)
+  float mloc0 = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+  if constexpr (N == 8) mloc0 = fmaxf(mloc0, fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+  if (__any(mloc0 > m + kLazy)) {     // wave-uniform
+    float mloc = fmaxf(mloc0, __shfl_xor(mloc0, 16));
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+    const float m_new = fmaxf(m, mloc);
+    // exp2 of a non-positive argument; m = -inf gives 0
+    const float alpha = (m_new == m) ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+    l *= alpha;
+#pragma unroll
+    for (int et = 0; et < ET; ++et) o[et] *= alpha;
+    m = m_new;
+  }
+  return (m == -INFINITY) ? 0.f : m;
+}
+
+// fp32 tile compute on ring stage SOFF / STAGE, on the fp32 matrix cores: the
+// same ring, plan and epilogue as bf16, with every product and sum in fp32.
+// Bound by HBM at up to 16 rows per item (one wave) and by the fp32 MFMAs
+// beyond; measured, attention call over 32 requests of 512-2048 keys: 8 heads
+// x d = 64 (163 MB of K/V) 39.6 us against 174 us for a VALU kernel of one
+// 256-thread work-group per item, d = 128 65 against 471, 32 query heads on 8
+// KV heads with 15-node trees (60 rows) at d = 64 94 against 1150.
+// (v_mfma_f32_16x16x4_f32: lane l holds A[l % 16][l / 16] and B[l / 16][l %
+// 16], one float each).  The contraction index of a product may be taken in
+// any order that A and B share, so both operands are read 16 bytes at a
+// time: K chunk 4 j + grp of key row l16 serves four score products (the
+// query's chunks sit in registers in the same order), and 16 bytes of V row
+// 4 grp + i serve four output tiles, whose row m then is column 4 m + x.  The
+// C layout leaves lane group g keys 4g .. 4g+3 of its query row, so the
+// probabilities are the PV product's B operand as they are, in fp32.
+template <int D, int SOFF>
+__device__ __forceinline__ void compute_tile_f32(const char* ring, RowTile<float, D>& S, int t0, int ke, int ctx,
+                                                 float scale_log2, int lane) {
+  using G = Geo<float, D>;
+  constexpr int KT = G::TK / 16, KS = RowTile<float, D>::KS;
+  const char* stage = ring + SOFF;
+  const int grp = lane >> 4, l16 = lane & 15;
+  f32x4 s[KT];
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) s[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    f32x4 kop[KT];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) kop[kt] = *reinterpret_cast<const f32x4*>(stage + S.koff[ks] + kt * 16 * G::ROWB);
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+        s[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kop[kt][x], S.q[ks][x], s[kt], 0, 0, 0);
+  }
+  float sv[4 * KT];
+  if (t0 + G::TK <= min(ke, ctx)) {   // wave-uniform: every key visible to every row
+#pragma unroll
+    for (int x = 0; x < 4 * KT; ++x) sv[x] = s[x >> 2][x & 3] * scale_log2;
+  } else {
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int t = t0 + 16 * kt + 4 * grp + i;
+        const float x = s[kt][i] * scale_log2;
+        sv[kt * 4 + i] = (t >= ke || !visible(t, ctx, S.anc)) ? -INFINITY : x;
+      }
+  }
+  const float m_use = lazy_reference(sv, S.m, S.l, S.o);
+  float psum = 0.f;
+#pragma unroll
+  for (int x = 0; x < 4 * KT; ++x) {
+    sv[x] = __builtin_amdgcn_exp2f(sv[x] - m_use);
+    psum += sv[x];
+  }
+  S.l += psum;
+  const char* vb = stage + G::MAT + (4 * grp) * G::ROWB + l16 * 16;
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int h = 0; h < D / 64; ++h) {
+        const f32x4 vop = *reinterpret_cast<const f32x4*>(vb + (16 * kt + i) * G::ROWB + h * 256);
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          S.o[4 * h + x] = __builtin_amdgcn_mfma_f32_16x16x4f32(vop[x], sv[4 * kt + i], S.o[4 * h + x], 0, 0, 0);
+      }
+}
 
 // Tile compute on ring stage SOFF / STAGE (a compile-time byte offset into
 // `ring`), so every LDS read of the stage carries its offset as an immediate
 // and the per-lane address registers are shared by all stages.
 template <int D, int SOFF>
-__device__ __forceinline__ void compute_tile(const char* ring, RowTile<D>& S, int t0, int ke, int ctx,
+__device__ __forceinline__ void compute_tile(const char* ring, RowTile<uint16_t, D>& S, int t0, int ke, int ctx,
                                              float scale_log2, int lane) {
-  using G = Geo<D>;
+  using G = Geo<uint16_t, D>;
   const char* stage = ring + SOFF;
   constexpr int KS = D / 32, ET = D / 16;
   const int grp = lane >> 4;
@@ -270,11 +373,7 @@ __device__ __forceinline__ void compute_tile(const char* ring, RowTile<D>& S, in
     }
     s[kt] = acc;
   }
-  // Scores in log2 units.  The exponent reference S.m trails the running max
-  // by at most kLazy: it moves (and O, l are rescaled) only when a score
-  // exceeds it by more than that, so p <= 2^kLazy and the common tile leaves
-  // the accumulators to the matrix cores alone.
-  constexpr float kLazy = 8.f;
+  // Scores in log2 units.
   float sv[8];
   if (t0 + 32 <= min(ke, ctx)) {      // wave-uniform: every key visible to every row
 #pragma unroll
@@ -290,21 +389,7 @@ __device__ __forceinline__ void compute_tile(const char* ring, RowTile<D>& S, in
       }
     }
   }
-  // this lane's largest score (a masked -inf never wins over a finite one)
-  const float mloc0 = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])),
-                            fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-  if (__any(mloc0 > S.m + kLazy)) {   // wave-uniform
-    float mloc = fmaxf(mloc0, __shfl_xor(mloc0, 16));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-    const float m_new = fmaxf(S.m, mloc);
-    // exp2 of a non-positive argument; S.m = -inf gives 0
-    const float alpha = (m_new == S.m) ? 1.f : __builtin_amdgcn_exp2f(S.m - m_new);
-    S.l *= alpha;
-#pragma unroll
-    for (int et = 0; et < ET; ++et) S.o[et] *= alpha;
-    S.m = m_new;
-  }
-  const float m_use = (S.m == -INFINITY) ? 0.f : S.m;
+  const float m_use = lazy_reference(sv, S.m, S.l, S.o);
   // p = 2^(score - m) <= 2^kLazy with the hardware exp2 (arguments are at most
   // kLazy; results below the normal range flush to zero, negligible against l >= 1
   // once a row has a finite score).  p is split into bf16 hi + lo so the PV
@@ -360,9 +445,9 @@ __device__ __forceinline__ void compute_tile(const char* ring, RowTile<D>& S, in
   }
 }
 
-template <int D, int W, int NS>
+template <typename T, int D, int W, int NS>
 struct AttnLds {
-  static constexpr int RING = NS * Geo<D>::STAGE;
+  static constexpr int RING = NS * Geo<T, D>::STAGE;
   static constexpr int OUT = W * 16 * (D + 4) * 4;  // fp32 output staging, padded rows
   static constexpr int BYTES = RING > OUT ? RING : OUT;
 };
@@ -531,15 +616,17 @@ __device__ __forceinline__ void combine_stream(const AttnParams& p, const AttnIt
 // resource based at its page, built from the block table entry (a
 // wave-uniform load, clamped into the pool, issued one ring step ahead of its
 // use); everything else is the packed path's code.
-template <int D, int W, int NS, int PG>
+template <typename T, int D, int W, int NS, int PG>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WavesPerEu<W>::value)))
 void attn_split_mfma(AttnParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass needs the signature only
-  using G = Geo<D>;
-  constexpr int ET = D / 16, KS = D / 32;
-  constexpr int PER = Xfer<D, W>::PER;
+  using G = Geo<T, D>;
+  using RT = RowTile<T, D>;
+  constexpr int ET = D / 16, KS = RT::KS, TK = G::TK, EB = (int)sizeof(T);
+  constexpr int PER = Xfer<T, D, W>::PER;
   static_assert(NS >= 2, "ring depth");
-  __shared__ __attribute__((aligned(1024))) char lds[AttnLds<D, W, NS>::BYTES];
+  static_assert(!(RT::F32 && PG), "paged caches are bf16");
+  __shared__ __attribute__((aligned(1024))) char lds[AttnLds<T, D, W, NS>::BYTES];
 
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -571,34 +658,34 @@ void attn_split_mfma(AttnParams p) {
   const int n = it.nq;
   const int R = it.nheads * n;
   const int ctx = it.ctx;
-  const int row_bytes = (int)(p.kv_st * 2);
-  const char* Kb = static_cast<const char*>(p.k) + ((int64_t)it.kv0 * p.kv_st + (int64_t)it.kvh * p.kv_sh) * 2;
-  const char* Vb = static_cast<const char*>(p.v) + ((int64_t)it.kv0 * p.kv_st + (int64_t)it.kvh * p.kv_sh) * 2;
-  const int ntiles = (it.ke - it.kb + 31) / 32;
+  const int row_bytes = (int)(p.kv_st * EB);
+  const char* Kb = static_cast<const char*>(p.k) + ((int64_t)it.kv0 * p.kv_st + (int64_t)it.kvh * p.kv_sh) * EB;
+  const char* Vb = static_cast<const char*>(p.v) + ((int64_t)it.kv0 * p.kv_st + (int64_t)it.kvh * p.kv_sh) * EB;
+  const int ntiles = (it.ke - it.kb + TK - 1) / TK;
   // byte range of this request's rows for this KV head (the host keeps it < 2^31)
   const int range = (it.ctx + it.nq) * row_bytes;
   const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)Kb, 0, range, 0x00020000);
   const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)Vb, 0, range, 0x00020000);
-  RowTile<D> S;
+  RT S;
   // This lane's B operand of the score product straight from HBM: query row
-  // 16w + c16 (padding rows repeat the item's row 0), columns 32ks + 8grp ..
-  // +7.  These loads are older than every tile transfer, so the wait after
+  // 16w + c16 (padding rows repeat the item's row 0), 16-byte chunks 4ks +
+  // grp.  These loads are older than every tile transfer, so the wait after
   // the ring's prologue below covers them without draining the ring.
   {
     int rr = w * 16 + c16;
     if (rr >= R) rr = 0;
     const int hh = rr / n, j = rr - hh * n;
     const char* src = static_cast<const char*>(p.q) +
-                      ((int64_t)(it.q0 + j) * p.q_st + (int64_t)(it.head_lo + hh) * p.q_sh) * 2 + grp * 16;
+                      ((int64_t)(it.q0 + j) * p.q_st + (int64_t)(it.head_lo + hh) * p.q_sh) * EB + grp * 16;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) S.q[ks] = *reinterpret_cast<const bf16x8*>(src + ks * 64);
+    for (int ks = 0; ks < KS; ++ks) S.q[ks] = *reinterpret_cast<const typename RT::QV*>(src + ks * 64);
   }
 
-  XferPlan<D, W> X;
+  XferPlan<T, D, W> X;
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     int row;
-    X.off[q] = xfer_offset<D>((w + q * W) % Xfer<D, W>::NI, lane, row_bytes, &row);
+    X.off[q] = xfer_offset<T, D>((w + q * W) % Xfer<T, D, W>::NI, lane, row_bytes, &row);
   }
 
   // paged: this KV head's slice of page 0 of each pool, the item's block
@@ -612,7 +699,7 @@ void attn_split_mfma(AttnParams p) {
   // consumer's wait would drain the whole ring every tile.
   typedef __attribute__((address_space(4))) const int32_t cint32_t;
   const cint32_t* btr = PG ? (const cint32_t*)(p.bt + (int64_t)it.req * p.bt_stride) : nullptr;
-  const int last_t0 = it.kb + 32 * (ntiles - 1);
+  const int last_t0 = it.kb + TK * (ntiles - 1);
   // (generic lambdas: instantiated only in the device pass, like the ring loop's)
   auto page_of = [&](auto t) -> int {
     const int t0 = min(it.kb + 32 * t, last_t0);
@@ -632,7 +719,7 @@ void attn_split_mfma(AttnParams p) {
       const int t0 = min(it.kb + 32 * t, last_t0);
       const int base = t0 - t0 % p.page_tokens;          // the page's first logical key
       const int pk0 = pg * p.page_tokens;                // the page's first physical key
-      issue_tile<D, W>(stage, qk, qv, row_bytes, pk0 + (t0 - base), pk0 + (it.ke - base), w, lane, X);
+      issue_tile<T, D, W>(stage, qk, qv, row_bytes, pk0 + (t0 - base), pk0 + (it.ke - base), w, lane, X);
     } else if constexpr (PG == 1) {
       const int t0 = min(it.kb + 32 * t, last_t0);
       const int base = t0 - t0 % p.page_tokens;          // the page's first logical key
@@ -640,10 +727,10 @@ void attn_split_mfma(AttnParams p) {
       const int prange = p.page_tokens * row_bytes;
       const __amdgpu_buffer_rsrc_t pk = __builtin_amdgcn_make_buffer_rsrc((void*)(Kh + pb), 0, prange, 0x00020000);
       const __amdgpu_buffer_rsrc_t pv = __builtin_amdgcn_make_buffer_rsrc((void*)(Vh + pb), 0, prange, 0x00020000);
-      issue_tile<D, W>(stage, pk, pv, row_bytes, t0 - base, it.ke - base, w, lane, X);
+      issue_tile<T, D, W>(stage, pk, pv, row_bytes, t0 - base, it.ke - base, w, lane, X);
     } else {
       (void)pg;
-      issue_tile<D, W>(stage, rk, rv, row_bytes, it.kb + 32 * t, it.ke, w, lane, X);
+      issue_tile<T, D, W>(stage, rk, rv, row_bytes, it.kb + TK * t, it.ke, w, lane, X);
     }
   };
 
@@ -665,14 +752,16 @@ void attn_split_mfma(AttnParams p) {
     S.l = 0.f;
 #pragma unroll
     for (int et = 0; et < ET; ++et) S.o[et] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int rk0 = 8 * (c16 >> 2) + (c16 & 3);
+    const int rk0 = RT::F32 ? c16 : 8 * (c16 >> 2) + (c16 & 3);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) S.koff[ks] = rk0 * G::ROWB + (((ks * 4 + grp) ^ swk<D>(rk0)) * 16);
-    const int rv0 = 8 * grp + (c16 >> 2);
-    const uint32_t ring_lds = (uint32_t)(uintptr_t)lds;
+    for (int ks = 0; ks < KS; ++ks) S.koff[ks] = rk0 * G::ROWB + (((ks * 4 + grp) ^ swk<T, D>(rk0)) * 16);
+    if constexpr (!RT::F32) {
+      const int rv0 = 8 * grp + (c16 >> 2);
+      const uint32_t ring_lds = (uint32_t)(uintptr_t)lds;
 #pragma unroll
-    for (int et = 0; et < ET; ++et)
-      S.voff[et] = ring_lds + rv0 * G::ROWB + (((2 * et + ((c16 & 3) >> 1)) ^ swv<D>(rv0)) * 16) + (c16 & 1) * 8;
+      for (int et = 0; et < ET; ++et)
+        S.voff[et] = ring_lds + rv0 * G::ROWB + (((2 * et + ((c16 & 3) >> 1)) ^ swv<T, D>(rv0)) * 16) + (c16 & 1) * 8;
+    }
   }
   const bool active = w * 16 < R;     // wave-uniform: this wave has query rows
 
@@ -685,7 +774,7 @@ void attn_split_mfma(AttnParams p) {
 #pragma unroll
   for (int st = 0; st < NS - 1; ++st) issue(lds + st * G::STAGE, st, PG ? page_of(st) : 0);
   // this wave's transfers per tile: PER, or PER - 1 on the last waves of an uneven split
-  const bool full_wave = Xfer<D, W>::EVEN || w < Xfer<D, W>::FULL;
+  const bool full_wave = Xfer<T, D, W>::EVEN || w < Xfer<T, D, W>::FULL;
   if (full_wave) wait_vm<PER * (NS - 1)>();
   else wait_vm<(PER - 1) * (NS - 1)>();
 #pragma unroll
@@ -727,7 +816,10 @@ void attn_split_mfma(AttnParams p) {
       if (t == 0) tr_first = wall_clock64();
 #endif
       if (t + NS - 1 < ntiles) issue(lds + ((st + NS - 1) % NS) * G::STAGE, t + NS - 1, pg_next);
-      if (active) compute_tile<D, st * G::STAGE>(lds, S, it.kb + 32 * t, it.ke, ctx, p.scale_log2, lane);
+      if (active) {
+        if constexpr (RT::F32) compute_tile_f32<D, st * G::STAGE>(lds, S, it.kb + TK * t, it.ke, ctx, p.scale_log2, lane);
+        else compute_tile<D, st * G::STAGE>(lds, S, it.kb + TK * t, it.ke, ctx, p.scale_log2, lane);
+      }
     });
   }
   wait_vm<0>();
@@ -742,10 +834,21 @@ void attn_split_mfma(AttnParams p) {
   l += __shfl_xor(l, 32);
   float* ost = reinterpret_cast<float*>(lds) + w * 16 * (D + 4);
   const float scale = it.seg < 0 ? 1.f / l : 1.f;
+  // bf16: output tile et holds columns 16 et + m; fp32: tile 4 h + x columns 64 h + 4 m + x
+  if constexpr (RT::F32) {
 #pragma unroll
-  for (int et = 0; et < ET; ++et) {
-    const f32x4 v = S.o[et] * scale;
-    *reinterpret_cast<float4*>(ost + c16 * (D + 4) + et * 16 + 4 * grp) = make_float4(v[0], v[1], v[2], v[3]);
+    for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4*>(ost + c16 * (D + 4) + 64 * h + 16 * grp + 4 * i) =
+            make_float4(S.o[4 * h][i] * scale, S.o[4 * h + 1][i] * scale, S.o[4 * h + 2][i] * scale,
+                        S.o[4 * h + 3][i] * scale);
+  } else {
+#pragma unroll
+    for (int et = 0; et < ET; ++et) {
+      const f32x4 v = S.o[et] * scale;
+      *reinterpret_cast<float4*>(ost + c16 * (D + 4) + et * 16 + 4 * grp) = make_float4(v[0], v[1], v[2], v[3]);
+    }
   }
   // output row of query row r (rows outside the destination are never written)
   auto out_row = [&](int r) -> int64_t {
@@ -820,117 +923,6 @@ void attn_split_mfma(AttnParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 (or widened bf16) VALU path: one 256-thread work-group per item,
-// 64-key tiles staged in LDS.  Used for fp32 inputs, whose products the bf16
-// matrix cores cannot take without rounding.
-// Rows per item <= kValuRows(D) = 4096 / D, 16 output values per thread.
-// ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ float load_elem(const T* p, int64_t i);
-template <>
-__device__ __forceinline__ float load_elem<float>(const float* p, int64_t i) { return p[i]; }
-
-template <typename T, int D>
-__global__ __launch_bounds__(256) void attn_split_valu(AttnParams p) {
-  constexpr int TK = 64;
-  constexpr int RV = 4096 / D;           // max rows per item
-  constexpr int OPT = RV * D / 256;      // outputs per thread (16)
-  __shared__ float qs[RV][D + 1];
-  __shared__ float ks[TK][D + 1];
-  __shared__ float vs[TK][D];
-  __shared__ float ps[RV][TK];
-  __shared__ float alpha_s[RV];
-  __shared__ float ml_s[RV][2];
-
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const AttnItem it = p.items[blockIdx.x];
-  mirror_plan(p);
-  const int n = it.nq;
-  const int R = it.nheads * n;
-  const int ctx = it.ctx;
-  const T* Kb = static_cast<const T*>(p.k) + (int64_t)it.kv0 * p.kv_st + (int64_t)it.kvh * p.kv_sh;
-  const T* Vb = static_cast<const T*>(p.v) + (int64_t)it.kv0 * p.kv_st + (int64_t)it.kvh * p.kv_sh;
-
-  for (int x = tid; x < RV * D; x += 256) {
-    const int r = x / D, e = x % D;
-    float val = 0.f;
-    if (r < R) {
-      const int hh = r / n, j = r - hh * n;
-      val = load_elem<T>(static_cast<const T*>(p.q),
-                         (int64_t)(it.q0 + j) * p.q_st + (int64_t)(it.head_lo + hh) * p.q_sh + e);
-    }
-    qs[r][e] = val;
-  }
-  for (int r = tid; r < RV; r += 256) {
-    ml_s[r][0] = -INFINITY;
-    ml_s[r][1] = 0.f;
-  }
-  float o[OPT];
-#pragma unroll
-  for (int x = 0; x < OPT; ++x) o[x] = 0.f;
-
-  for (int t0 = it.kb; t0 < it.ke; t0 += TK) {
-    __syncthreads();
-    for (int x = tid; x < TK * D; x += 256) {
-      const int t = x / D, e = x % D;
-      const int key = min(t0 + t, it.ke - 1);
-      ks[t][e] = load_elem<T>(Kb, (int64_t)key * p.kv_st + e);
-      vs[t][e] = load_elem<T>(Vb, (int64_t)key * p.kv_st + e);
-    }
-    __syncthreads();
-    const int t = t0 + lane;
-    for (int r = wv; r < R; r += 4) {
-      float s = 0.f;
-#pragma unroll 8
-      for (int e = 0; e < D; ++e) s += qs[r][e] * ks[lane][e];
-      const int j = r % n;
-      s *= p.scale_log2;
-      const uint32_t anc = p.per_req ? p.nodes[it.node0 + j].anc : p.anc[j];
-      if (t >= it.ke || !visible(t, ctx, anc)) s = -INFINITY;
-      const float m_old = ml_s[r][0];
-      const float m_new = fmaxf(m_old, wave_max(s));
-      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-      const float pv = exp2f(s - m_use);
-      const float psum = wave_sum(pv);
-      ps[r][lane] = pv;
-      if (lane == 0) {
-        const float a = exp2f(m_old - m_use);
-        alpha_s[r] = a;
-        ml_s[r][0] = m_new;
-        ml_s[r][1] = ml_s[r][1] * a + psum;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int x = 0; x < OPT; ++x) {
-      const int idx = tid + 256 * x;
-      const int r = idx / D, e = idx % D;
-      if (r < R) {
-        float acc = o[x] * alpha_s[r];
-#pragma unroll 8
-        for (int tt = 0; tt < TK; ++tt) acc += ps[r][tt] * vs[tt][e];
-        o[x] = acc;
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int x = 0; x < OPT; ++x) {
-    const int idx = tid + 256 * x;
-    const int r = idx / D, e = idx % D;
-    if (r >= R) continue;
-    const int hh = r / n, j = r - hh * n, h = it.head_lo + hh;
-    if (it.seg < 0) {
-      p.out[((int64_t)(it.q0 + j) * p.Hq + h) * D + e] = o[x] / ml_s[r][1];
-    } else {
-      const int64_t pr = (int64_t)it.part0 + ((int64_t)it.seg * n + j) * p.Hq + h;
-      p.part_o[pr * D + e] = o[x];
-      if (e == 0) p.part_ml[pr] = make_float2(ml_s[r][0], ml_s[r][1]);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Split combine: one wave per (query row, head) of a request with nseg > 1.
 //   O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, splits in fixed order.
 // ---------------------------------------------------------------------------
@@ -995,18 +987,38 @@ __global__ __launch_bounds__(256) void attn_combine(AttnParams p) {
   for (int x = 0; x < PER; ++x) p.out[((int64_t)qrow * p.Hq + h) * D + lane + 64 * x] = acc[x] * inv;
 }
 
-template <int D, int PG>
-hipError_t launch_mfma(const AttnParams& p, int nr, hipStream_t s) {
-  const dim3 grid(p.grid);
+// The split kernel's builds: the layout and input type, the head dim and the
+// waves per work-group.
+struct Build {
+  void (*kern)(AttnParams) = nullptr;
+  int threads = 0, lds = 0;
+};
+template <typename T, int D, int PG>
+Build build_of(int nr) {
+  auto make = [](auto w, auto ns) {
+    constexpr int W = decltype(w)::value, NS = decltype(ns)::value;
+    return Build{attn_split_mfma<T, D, W, NS, PG>, 64 * W, AttnLds<T, D, W, NS>::BYTES};
+  };
+  constexpr bool F32 = sizeof(T) == 4;
   switch (nr) {
-    case 1: attn_split_mfma<D, 1, SV_NS_W1, PG><<<grid, dim3(64), 0, s>>>(p); break;
-    case 2: attn_split_mfma<D, 2, SV_NS_W2, PG><<<grid, dim3(128), 0, s>>>(p); break;
-    case 3: attn_split_mfma<D, 3, SV_NS_W3, PG><<<grid, dim3(192), 0, s>>>(p); break;
-    case 4: attn_split_mfma<D, 4, SV_NS_W4, PG><<<grid, dim3(256), 0, s>>>(p); break;
-    case 5: attn_split_mfma<D, 5, SV_NS_W5, PG><<<grid, dim3(320), 0, s>>>(p); break;
-    default: return hipErrorInvalidValue;
+    case 1: return make(std::integral_constant<int, 1>{}, std::integral_constant<int, F32 ? SV_NS_F32 : SV_NS_W1>{});
+    case 2: return make(std::integral_constant<int, 2>{}, std::integral_constant<int, F32 ? SV_NS_F32 : SV_NS_W2>{});
+    case 3: return make(std::integral_constant<int, 3>{}, std::integral_constant<int, F32 ? SV_NS_F32 : SV_NS_W3>{});
+    case 4: return make(std::integral_constant<int, 4>{}, std::integral_constant<int, F32 ? SV_NS_F32 : SV_NS_W4>{});
+    case 5:
+      if constexpr (!F32) return make(std::integral_constant<int, 5>{}, std::integral_constant<int, SV_NS_W5>{});
   }
-  return hipGetLastError();
+  return Build{};
+}
+Build find_build(int D, int nr, int layout) {
+  if (D != 64 && D != 128) return Build{};
+  switch (layout) {
+    case kAttnPacked: return D == 64 ? build_of<uint16_t, 64, 0>(nr) : build_of<uint16_t, 128, 0>(nr);
+    case kAttnPaged: return D == 64 ? build_of<uint16_t, 64, 1>(nr) : build_of<uint16_t, 128, 1>(nr);
+    case kAttnPaged32: return D == 64 ? build_of<uint16_t, 64, 2>(nr) : build_of<uint16_t, 128, 2>(nr);
+    case kAttnF32: return D == 64 ? build_of<float, 64, 0>(nr) : build_of<float, 128, 0>(nr);
+    default: return Build{};
+  }
 }
 
 }  // namespace
@@ -1017,78 +1029,34 @@ extern "C" __attribute__((visibility("default"))) int sv_attn_trace_copy(void* d
 }
 #endif
 
-int max_rows_per_item(int dtype_bf16, int D) { return dtype_bf16 ? 80 : 4096 / D; }
+int max_rows_per_item(int layout) { return layout == kAttnF32 ? 64 : 80; }
 
-int attn_lds_bytes(int D, int nr) {
-  auto bytes = [&](auto d) -> int {
-    constexpr int DD = decltype(d)::value;
-    switch (nr) {
-      case 1: return AttnLds<DD, 1, SV_NS_W1>::BYTES;
-      case 2: return AttnLds<DD, 2, SV_NS_W2>::BYTES;
-      case 3: return AttnLds<DD, 3, SV_NS_W3>::BYTES;
-      case 4: return AttnLds<DD, 4, SV_NS_W4>::BYTES;
-      case 5: return AttnLds<DD, 5, SV_NS_W5>::BYTES;
-      default: return 0;
-    }
-  };
-  return D == 64 ? bytes(std::integral_constant<int, 64>{}) : bytes(std::integral_constant<int, 128>{});
-}
+int attn_lds_bytes(int D, int nr, int layout) { return find_build(D, nr, layout).lds; }
 
-int attn_resident_per_cu(int D, int nr, int paged) {
-  // per (D, waves, paged) build, asked once: the device's own placement
-  static std::atomic<int> cache[2][5][3] = {};
-  if ((D != 64 && D != 128) || nr < 1 || nr > 5) return 0;
-  if (paged < 0 || paged > 2) return 0;
-  std::atomic<int>& slot = cache[D == 128][nr - 1][paged];
+int attn_resident_per_cu(int D, int nr, int layout) {
+  // per build, asked once: the device's own placement
+  static std::atomic<int> cache[2][5][kAttnLayouts] = {};
+  const Build k = find_build(D, nr, layout);
+  if (!k.kern) return 0;
+  std::atomic<int>& slot = cache[D == 128][nr - 1][layout];
   int v = slot.load(std::memory_order_relaxed);
   if (v != 0) return v > 0 ? v : 0;
-  auto ask = [](auto kern, int threads) {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, threads, 0) != hipSuccess) {
-      (void)hipGetLastError();
-      return -1;
-    }
-    return n > 0 ? n : -1;
-  };
-  auto by_build = [&](auto d, auto pg) -> int {
-    constexpr int DD = decltype(d)::value;
-    constexpr int PP = decltype(pg)::value;
-    switch (nr) {
-      case 1: return ask(attn_split_mfma<DD, 1, SV_NS_W1, PP>, 64);
-      case 2: return ask(attn_split_mfma<DD, 2, SV_NS_W2, PP>, 128);
-      case 3: return ask(attn_split_mfma<DD, 3, SV_NS_W3, PP>, 192);
-      case 4: return ask(attn_split_mfma<DD, 4, SV_NS_W4, PP>, 256);
-      default: return ask(attn_split_mfma<DD, 5, SV_NS_W5, PP>, 320);
-    }
-  };
-  using I64 = std::integral_constant<int, 64>;
-  using I128 = std::integral_constant<int, 128>;
-  using P0 = std::integral_constant<int, 0>;
-  using P1 = std::integral_constant<int, 1>;
-  using P2 = std::integral_constant<int, 2>;
-  v = D == 64 ? (paged == 2 ? by_build(I64{}, P2{}) : paged == 1 ? by_build(I64{}, P1{}) : by_build(I64{}, P0{}))
-              : (paged == 2 ? by_build(I128{}, P2{}) : paged == 1 ? by_build(I128{}, P1{}) : by_build(I128{}, P0{}));
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, reinterpret_cast<const void*>(k.kern), k.threads, 0) !=
+      hipSuccess) {
+    (void)hipGetLastError();
+    v = -1;
+  }
+  if (v <= 0) v = -1;
   slot.store(v, std::memory_order_relaxed);
   return v > 0 ? v : 0;
 }
 
-hipError_t launch_attention(const AttnParams& p, int dtype_bf16, int nr_max, hipStream_t s) {
-  hipError_t e = hipSuccess;
-  if (p.n_items > 0) {
-    if (dtype_bf16 && p.bt) {
-      e = p.pool32 ? ((p.D == 64) ? launch_mfma<64, 2>(p, nr_max, s) : launch_mfma<128, 2>(p, nr_max, s))
-                   : ((p.D == 64) ? launch_mfma<64, 1>(p, nr_max, s) : launch_mfma<128, 1>(p, nr_max, s));
-    } else if (dtype_bf16) {
-      e = (p.D == 64) ? launch_mfma<64, 0>(p, nr_max, s) : launch_mfma<128, 0>(p, nr_max, s);
-    } else {
-      dim3 grid(p.n_items), block(256);
-      if (p.D == 64) attn_split_valu<float, 64><<<grid, block, 0, s>>>(p);
-      else attn_split_valu<float, 128><<<grid, block, 0, s>>>(p);
-      e = hipGetLastError();
-    }
-    if (e != hipSuccess) return e;
-  }
-  return e;
+hipError_t launch_attention(const AttnParams& p, int layout, int nr_max, hipStream_t s) {
+  if (p.n_items <= 0) return hipSuccess;
+  const Build k = find_build(p.D, nr_max, layout);
+  if (!k.kern) return hipErrorInvalidValue;
+  k.kern<<<dim3(p.grid), dim3(k.threads), 0, s>>>(p);
+  return hipGetLastError();
 }
 
 hipError_t launch_combine(const AttnParams& p, hipStream_t s) {

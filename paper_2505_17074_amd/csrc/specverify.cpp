@@ -39,6 +39,7 @@ struct Plan {
   Topo topo{};
   // attention
   bool has_attn = false;
+  int layout = sv::kAttnPacked;
   std::vector<AttnItem> items;
   int64_t parts = 0;      // partial rows
   int nr_max = 1;
@@ -167,16 +168,20 @@ int device_cus() {
   return cus[dev];
 }
 
-// Work-groups of the bf16 split kernel that run at once per compute unit.
-// Measured, not taken from the occupancy calculator (which allows 3 for the
-// 4- and 5-wave builds): with 64 equal streams cut into 8 pieces each (512
+// Work-groups of the split kernel that run at once per compute unit.
+// bf16: measured, not taken from the occupancy calculator (which allows 3 for
+// the 4- and 5-wave builds): with 64 equal streams cut into 8 pieces each (512
 // items on 256 compute units) every width, at d = 64 and d = 128, runs 7-27%
 // faster than with 9 pieces each (576 items), whose last 64 items form a
 // second, nearly empty round.
-#ifndef SV_GROUPS_W5
-#define SV_GROUPS_W5 2
-#endif
-int groups_per_cu(int waves) { return waves == 5 ? SV_GROUPS_W5 : 2; }
+// fp32: a tile takes its wave 64 fp32 MFMAs (2048 cycles for 16 KB of K and
+// V), so narrow work-groups need one per SIMD to keep up with HBM: 32 requests
+// x 8 KV heads of 512-2048 keys, d = 64, one wave: 2 per CU 51.6 us, 3 41.5,
+// 4 39.6, 5 39.6; two waves at d = 128: 2 per CU 113, 3 105, 4 105; wider
+// ones fill the SIMDs with two.
+int groups_per_cu(int waves, int layout, bool coarse) {
+  return coarse || layout != sv::kAttnF32 ? 2 : std::max(2, 5 - waves);
+}
 
 // Piece length for a stream of L >= 1 keys and a split of s >= 1 keys: the
 // stream cut into ceil(L / s) equal parts, rounded up to 32 keys (a short
@@ -255,9 +260,10 @@ int64_t claim_extra(int64_t n_items) {
 // Keys per piece of each request's streams (every KV head and head group of
 // a request has the same length).  `slots` = work-groups the device runs at
 // once; `len[i]` = keys of request i, each the length of `mult[i]` streams.
-// Pieces stay >= 40 * rows keys, so the fp32 partials (rows x d x 4 bytes,
-// written once and read once by the combine) remain a few percent of the K/V
-// bytes a piece streams (32 rows x d x 2 x 2 per 32 keys), and >= 256 keys.
+// Pieces stay >= 40 * rows keys (fp32 inputs: 20 * rows), so the fp32
+// partials (rows x d x 4 bytes, written once and read once by the combine)
+// remain a few percent of the K/V bytes a piece streams (32 x d x 2 x elem per
+// 32 keys), and >= 256 keys.
 //  - At least as many streams as slots: pieces of at most kMaxPiece keys
 //    (above), dispatched longest first.
 //  - Fewer streams than slots: every work-group takes exactly one item (a
@@ -270,9 +276,10 @@ int64_t claim_extra(int64_t n_items) {
 #ifndef SV_MIN_PIECE_ROWS
 #define SV_MIN_PIECE_ROWS 40
 #endif
-std::vector<int> piece_lengths(const std::vector<int>& len, const std::vector<int>& mult, int rows_max, int64_t slots) {
+std::vector<int> piece_lengths(const std::vector<int>& len, const std::vector<int>& mult, int rows_max, int elem,
+                               int64_t slots, bool coarse) {
   slots = std::max<int64_t>(slots, 1);
-  int64_t lo = std::max<int64_t>(SV_MIN_PIECE_ROWS * (int64_t)rows_max, 256);
+  int64_t lo = std::max<int64_t>(SV_MIN_PIECE_ROWS * 2 / (coarse ? 2 : elem) * (int64_t)rows_max, 256);
   lo = std::min<int64_t>((lo + 31) / 32 * 32, kMaxSplit);
   const size_t B = len.size();
   std::vector<int> out(B);
@@ -309,8 +316,10 @@ std::vector<int> piece_lengths(const std::vector<int>& len, const std::vector<in
   return out;
 }
 
+// `coarse`: fewer, longer pieces (less partial scratch), for a caller whose
+// scratch is fixed and too small for the automatic split.
 spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
-                         const spec_accept_args_t* acc, Plan& P) {
+                         const spec_accept_args_t* acc, Plan& P, bool coarse = false) {
   spec_status_t st = check_requests(r);
   if (st != SPEC_OK) return st;
   P.B = r->num_requests;
@@ -408,10 +417,14 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
       }
     }
     P.has_attn = true;
-    const int bf = attn->dtype == SPEC_BF16;
+    P.layout = attn->dtype == SPEC_F32 ? sv::kAttnF32
+               : !attn->block_table
+                   ? sv::kAttnPacked
+                   : sv::paged_layout(attn->num_pages, (int64_t)attn->page_tokens * attn->kv_stride_tok * 2);
+    const bool bf = attn->dtype == SPEC_BF16;
     const int D = attn->head_dim;
     const int Hq = attn->num_q_heads, Hkv = attn->num_kv_heads, G = Hq / Hkv;
-    const int rmax = sv::max_rows_per_item(bf, D);
+    const int rmax = sv::max_rows_per_item(P.layout);
     // query-head groups per request so that heads * n_i <= rmax
     std::vector<int> groups(P.B), hpg(P.B), len(P.B), mult(P.B);
     int rows_max = 1;
@@ -425,13 +438,13 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
       mult[i] = Hkv * groups[i];
       rows_max = std::max(rows_max, hpg[i] * n);
     }
-    const int64_t slots = (int64_t)device_cus() * (bf ? groups_per_cu((rows_max + 15) / 16) : 2);
+    const int64_t slots = (int64_t)device_cus() * groups_per_cu((rows_max + 15) / 16, P.layout, coarse);
     std::vector<int> plen;
     if (attn->split_kv > 0) {
       plen.resize(P.B);
       for (int i = 0; i < P.B; ++i) plen[i] = piece_len(len[i], attn->split_kv);
     } else {
-      plen = piece_lengths(len, mult, rows_max, slots);
+      plen = piece_lengths(len, mult, rows_max, (int)elem, slots, coarse);
     }
     P.split = 0;
     for (int i = 0; i < P.B; ++i) P.split = std::max(P.split, plen[i]);
@@ -498,9 +511,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
     // the claim word whenever there are more items than slots, whatever the
     // device reports.
     const int64_t n_it = (int64_t)P.items.size();
-    const int build = !attn->block_table ? 0
-                      : sv::paged_build(attn->num_pages, (int64_t)attn->page_tokens * attn->kv_stride_tok * 2);
-    const int64_t resident = (int64_t)device_cus() * sv::attn_resident_per_cu(D, nr, build);
+    const int64_t resident = (int64_t)device_cus() * sv::attn_resident_per_cu(D, nr, P.layout);
     const int64_t first = claim_first_round(std::max(slots, resident));
     P.first_round = P.grid = n_it;
     P.claim_word = bf && n_it > std::min(first, slots);
@@ -524,7 +535,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
         blk = std::max<int64_t>(blk, (int64_t)q.nseg * q.nq * Hq * D * 4);
         stream_bytes = std::max<int64_t>(stream_bytes, rows * q.nseg * D * 4);
       }
-      P.fused = lds <= sv::attn_lds_bytes(D, nr) && blk < ((int64_t)1 << 31) && stream_bytes <= fuse_max_bytes();
+      P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) && stream_bytes <= fuse_max_bytes();
     }
   }
 
@@ -638,6 +649,7 @@ struct RunMode {
   std::mutex* staging_mu = nullptr;   // held while the staging is written and the copy enqueued
   const spec_lm_head_args_t* lm = nullptr;   // the LM head runs first, its statistics replace the row pass
   size_t off_tiles = 0;       // its tile statistics in the workspace
+  bool coarse = false;        // the plan with less partial scratch (build_plan)
 };
 
 spec_status_t check_lm(const spec_lm_head_args_t* lm) {
@@ -672,7 +684,7 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
                   void* ws, size_t ws_bytes, void* staging, size_t staging_bytes, void* stream,
                   const RunMode& mode = RunMode()) {
   Plan P;
-  spec_status_t st = build_plan(req, attn, acc, P);
+  spec_status_t st = build_plan(req, attn, acc, P, mode.coarse);
   if (st != SPEC_OK) return st;
   if (!ws || (reinterpret_cast<uintptr_t>(ws) % kAlign) || ws_bytes < P.device_bytes) return SPEC_ERR_WORKSPACE;
   if (!staging || staging_bytes < P.plan_bytes) return SPEC_ERR_WORKSPACE;
@@ -720,8 +732,7 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
       a.counters = reinterpret_cast<unsigned long long*>(d + P.off_counters);
       a.fused = 1;
     } else if (P.parts > 0 && pl != d) {      // the combine kernel runs: mirror its table and map
-      const bool mfma = attn->dtype == SPEC_BF16;
-      const int64_t threads = mfma ? 64 * (int64_t)P.nr_max : 256;
+      const int64_t threads = 64 * (int64_t)P.nr_max;
       const int64_t n16 = (int64_t)(P.off_items / 16);
       a.mirror_src = reinterpret_cast<const uint4*>(pl);
       a.mirror_dst = reinterpret_cast<uint4*>(d);
@@ -743,7 +754,6 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
     a.num_pages = attn->num_pages;
     a.page_bytes = (int64_t)attn->page_tokens * attn->kv_stride_tok * 2;
     a.pool_bytes = (int64_t)attn->num_pages * a.page_bytes;
-    a.pool32 = attn->block_table && sv::paged_build(attn->num_pages, a.page_bytes) == 2 ? 1 : 0;
     std::memcpy(a.anc, P.topo.anc, sizeof(a.anc));
     a.nodes = reinterpret_cast<const sv::NodeInfo*>(pl + P.off_nodes);
     a.per_req = P.per_req ? 1 : 0;
@@ -862,7 +872,7 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
   auto launch_attn = [&](hipStream_t st) -> bool {
     if (attn->event_begin && hipEventRecord(static_cast<hipEvent_t>(attn->event_begin), st) != hipSuccess)
       return false;
-    if (sv::launch_attention(a, attn->dtype == SPEC_BF16, P.nr_max, st) != hipSuccess) return false;
+    if (sv::launch_attention(a, P.layout, P.nr_max, st) != hipSuccess) return false;
     if (P.parts > 0 && !P.fused && sv::launch_combine(a, st) != hipSuccess) return false;
     if (attn->event_end && hipEventRecord(static_cast<hipEvent_t>(attn->event_end), st) != hipSuccess) return false;
     return true;
@@ -934,13 +944,21 @@ spec_status_t spec_verify_noalloc(const spec_requests_t* req, const spec_attn_ar
   static char host_staging[sv::kNoAllocStagingBytes];
   static std::mutex staging_mu;
   if (!attn || !acc) return SPEC_ERR_INVALID_ARG;
+  RunMode mode;
+  auto fits = [](const Plan& P) {
+    return P.device_bytes <= sv::kNoAllocScratchBytes && P.plan_bytes <= sv::kNoAllocStagingBytes;
+  };
   Plan P;
-  const spec_status_t st = build_plan(req, attn, acc, P);   // argument checks before any HIP call
+  spec_status_t st = build_plan(req, attn, acc, P);   // argument checks before any HIP call
   if (st != SPEC_OK) return st;
-  if (P.device_bytes > sv::kNoAllocScratchBytes || P.plan_bytes > sv::kNoAllocStagingBytes) return SPEC_ERR_WORKSPACE;
+  if (!fits(P)) {
+    mode.coarse = true;
+    P = Plan();
+    if ((st = build_plan(req, attn, acc, P, true)) != SPEC_OK) return st;
+    if (!fits(P)) return SPEC_ERR_WORKSPACE;
+  }
   void* scratch = nullptr;
   if (sv::noalloc_scratch(&scratch) != hipSuccess) return SPEC_ERR_HIP;
-  RunMode mode;
   mode.overlap = false;
   mode.pageable = true;
   mode.staging_mu = &staging_mu;

@@ -62,13 +62,12 @@ struct AttnParams {
   int32_t num_pages;
   int64_t page_bytes;
   int64_t pool_bytes;        // num_pages * page_bytes
-  int32_t pool32;            // pool_bytes < 2^32: the paged build with one descriptor per item
   uint32_t anc[kMaxNodes];   // ancestors-or-self masks (kernel arguments: uniform loads)
   // per-request trees (per_req = 1): each request's masks in its node-table
   // entries, read where the host staged them
   const NodeInfo* nodes;
   int32_t per_req;
-  // Split combine inside the split kernel (bf16 path): each split stream's
+  // Split combine inside the split kernel (bf16 inputs): each split stream's
   // pieces check in on counters[stream] ((call tag << 32) | arrivals), and
   // the last one to arrive combines the stream's partials.  The tag is new
   // on every call, so a counter holding another call's value (or anything
@@ -76,7 +75,7 @@ struct AttnParams {
   unsigned long long* counters;
   uint32_t call_tag;
   int32_t fused;
-  // Work-groups of the bf16 split kernel (grid >= n_items).  Work-group b <
+  // Work-groups of the split kernel (grid >= n_items; more for bf16 inputs only).  Work-group b <
   // first_round takes item b; every later one claims the next item from
   // *claim ((call tag << 32) | next item; a word holding another tag starts
   // over at first_round) and leaves when none is left.  Later work-groups are
@@ -87,23 +86,27 @@ struct AttnParams {
   unsigned long long* claim;
 };
 
-// Largest number of query rows (heads x verify positions) one work item holds.
-int max_rows_per_item(int dtype_bf16, int D);
-
-hipError_t launch_attention(const AttnParams& p, int dtype_bf16, int nr_max, hipStream_t s);
-// Work-groups of the bf16 split kernel's build for head dim D, nr waves and
-// the paged or packed layout that one compute unit holds at once, as the
-// device reports it; 0 where it cannot be asked (no device).  paged: 0 the
-// packed build, 1 the paged build with a descriptor per tile, 2 the paged
-// build with one descriptor per item (pools whose byte offsets fit 32 bits).
-int attn_resident_per_cu(int D, int nr, int paged);
-// The paged build a launch with these pool sizes takes (1 or 2).
-inline int paged_build(int64_t num_pages, int64_t page_bytes) {
-  return num_pages * page_bytes <= (int64_t)0xFFFFFFFF ? 2 : 1;
+// The split kernel's builds by input type and K/V layout: bf16 packed, bf16
+// paged with a buffer descriptor per tile, bf16 paged with one descriptor per
+// item (pools whose byte offsets fit 32 bits), fp32 packed.
+enum AttnLayout { kAttnPacked = 0, kAttnPaged = 1, kAttnPaged32 = 2, kAttnF32 = 3, kAttnLayouts = 4 };
+// The paged build a launch with these pool sizes takes.
+inline int paged_layout(int64_t num_pages, int64_t page_bytes) {
+  return num_pages * page_bytes <= (int64_t)0xFFFFFFFF ? kAttnPaged32 : kAttnPaged;
 }
-// LDS bytes of the bf16 split kernel's build for head dim D and nr row tiles
-// (the fused combine stages its weights there).
-int attn_lds_bytes(int D, int nr);
+
+// Largest number of query rows (heads x verify positions) one work item
+// holds: 16 per wave, at most five waves (fp32: four).
+int max_rows_per_item(int layout);
+
+// nr_max: waves (16-row tiles) per work-group.
+hipError_t launch_attention(const AttnParams& p, int layout, int nr_max, hipStream_t s);
+// Work-groups of the split kernel's build for head dim D, nr waves and this
+// layout that one compute unit holds at once, as the device reports it; 0
+// where it cannot be asked (no device).
+int attn_resident_per_cu(int D, int nr, int layout);
+// LDS bytes of that build (the fused combine stages its weights there).
+int attn_lds_bytes(int D, int nr, int layout);
 hipError_t launch_combine(const AttnParams& p, hipStream_t s);
 
 }  // namespace sv
