@@ -64,13 +64,14 @@
  *     SPEC_ATTN_FIRST_ROUND (a work-group count >= 1) and SPEC_ATTN_EXTRA_WG
  *     (surplus work-groups >= 0) override the first round and the surplus;
  *     they exist for tests.
- *   - When the verify attention cuts a request's KV range into pieces, the
- *     last piece of each (request, KV head, head group) to finish combines
- *     the pieces' partial outputs (bf16 inputs, partial blocks up to 64 KB
- *     per stream); otherwise a separate combine kernel follows.  The
- *     environment variable SPEC_FUSED_COMBINE_MAX_BYTES (a byte count)
- *     replaces the 64 KB limit; the outputs agree either way within the
- *     attention tolerance, and each choice is deterministic.
+ *   - When the verify attention cuts a request's KV range into pieces, a
+ *     separate combine kernel follows, or, in batches of more than one round
+ *     of work-groups and with a caller's split_kv (bf16 inputs, partial blocks
+ *     up to 64 KB per stream), the last piece of each (request, KV head, head
+ *     group) to finish combines the pieces' partial outputs.  The environment
+ *     variable SPEC_FUSED_COMBINE_MAX_BYTES (a byte count) replaces that
+ *     choice's limit; the outputs agree either way within the attention
+ *     tolerance, and each choice is deterministic.
  *   - Results are deterministic: the same inputs give bit-identical outputs
  *     (fixed reduction orders, no floating-point atomics).
  *   - A call captured into a HIP graph may be replayed any number of times,
@@ -335,8 +336,10 @@ SPEC_API spec_status_t spec_accept(const spec_requests_t* req,
  * two parts are independent: the acceptance kernels run on a library-owned
  * side stream (one per device, created on first use at the default priority)
  * that forks from `stream` at the start of the call and is joined back into `stream`
- * before the call returns, overlapping the attention kernels.  Completion is
- * still ordered by `stream` alone. */
+ * before the call returns, overlapping the attention kernels; small steps
+ * (up to 128 MiB of keys and values), where the fork and join cost more than
+ * they hide, run both parts on `stream`.  Completion is ordered by `stream`
+ * alone either way. */
 SPEC_API spec_status_t spec_verify(const spec_requests_t* req,
                           const spec_attn_args_t* attn,
                           const spec_accept_args_t* acc,

@@ -42,6 +42,7 @@ struct Plan {
   int layout = sv::kAttnPacked;
   std::vector<AttnItem> items;
   int64_t parts = 0;      // partial rows
+  int64_t kv_bytes = 0;   // K and V bytes the attention reads
   int nr_max = 1;
   int split = 0;
   int64_t split_streams = 0;   // (request, KV head, head group) streams cut into pieces
@@ -192,24 +193,12 @@ int piece_len(int L, int64_t s) {
   return (int)(((L + n0 - 1) / n0 + 31) / 32 * 32);
 }
 
-// Keys per split piece.  `slots` = work-groups the device runs at once;
-// `len[i]` = keys of request i, each the length of `mult[i]` streams (one per
-// KV head and head group).  Pieces stay >= 40 * rows keys, so the fp32
-// partials (rows x d x 4 bytes, written once and read once by the combine)
-// remain a few percent of the K/V bytes a piece streams (32 rows x d x 2 x 2
-// per 32 keys), and >= 256 keys.
-//  - At least as many streams as slots: pieces of at most kMaxPiece keys,
-//    dispatched longest first, the items past the first round claimed at run
-//    time.  A work-group streams about 30 keys per microsecond, so a
-//    4096-key piece started first runs nearly as long as the whole kernel on
-//    a 128-request ragged batch (3200 keys per slot on average).  Measured
-//    there with claims, attention alone: 2048-key pieces 158 us, 2560 150,
-//    3072 146, 3328-3840 142-143, 4096 155 (and 155 without claims).
-//  - Fewer streams than slots: the smallest split whose items all fit one
-//    round of slots, so every work-group takes exactly one item and none waits
-//    for a second round (on 8 requests of 16K-32K keys x 8 KV heads, 504 items
-//    of <= 3264 keys: about 7% faster than 408 items of <= 4096 keys, and 24%
-//    faster than 528 items of <= 3072).
+// Longest piece when there are at least as many streams as slots
+// (piece_lengths below).  A work-group streams about 30 keys per microsecond,
+// so a 4096-key piece started first runs nearly as long as the whole kernel on
+// a 128-request ragged batch (3200 keys per slot on average).  Measured there
+// with run-time claims, attention alone: 2048-key pieces 158 us, 2560 150,
+// 3072 146, 3328-3840 142-143, 4096 155 (and 155 without claims).
 #ifndef SV_MAX_PIECE
 #define SV_MAX_PIECE 3584
 #endif
@@ -217,19 +206,22 @@ constexpr int64_t kMaxPiece = SV_MAX_PIECE;
 // Largest partial block (rows x pieces x d x 4 bytes) of one split stream
 // that the split kernel's last piece combines itself; above it the separate
 // combine kernel spreads the work over the device.  The last piece reads the
-// block alone, after every other piece of the stream has finished: on the
-// ragged GQA batch (streams of <= 55 KB) fusing shortens the attention by
-// 5 us and the step by 10 us, while on the long-context batch (295 KB per
-// stream) it lengthens the attention by 7 us.  The environment variable
+// block alone, after every other piece of the stream has finished: that pays
+// only while other items keep the device busy, so a one-round plan (fewer
+// streams than slots) never fuses by default.  Measured: the ragged GQA batch
+// (1024 streams, the few split ones <= 55 KB) 5 us shorter fused; one round,
+// fused against separate: 64 x 32K-key streams (295 KB) 158-166 against
+// 152.5 us, 8 streams of 1000 keys in 8 pieces 21.6 against 17.0, 16 streams
+// of 2000 keys (60 rows) in 16 pieces 40 against 19.  The environment variable
 // SPEC_FUSED_COMBINE_MAX_BYTES overrides the limit (tests use it to reach
 // the fused path with any stream).
 constexpr int64_t kFuseMaxBytes = 64 << 10;
-int64_t fuse_max_bytes() {
+int64_t fuse_max_bytes(int64_t dflt) {
   const char* e = std::getenv("SPEC_FUSED_COMBINE_MAX_BYTES");
-  if (!e || !*e) return kFuseMaxBytes;
+  if (!e || !*e) return dflt;
   char* end = nullptr;
   const long long v = std::strtoll(e, &end, 10);
-  return (end && *end == 0 && v >= 0) ? (int64_t)v : kFuseMaxBytes;
+  return (end && *end == 0 && v >= 0) ? (int64_t)v : dflt;
 }
 constexpr int64_t kMaxSplit = 1 << 20;
 // Work-groups launched beyond the item count when items are claimed at run
@@ -260,35 +252,47 @@ int64_t claim_extra(int64_t n_items) {
 // Keys per piece of each request's streams (every KV head and head group of
 // a request has the same length).  `slots` = work-groups the device runs at
 // once; `len[i]` = keys of request i, each the length of `mult[i]` streams.
-// Pieces stay >= 40 * rows keys (fp32 inputs: 20 * rows), so the fp32
-// partials (rows x d x 4 bytes, written once and read once by the combine)
-// remain a few percent of the K/V bytes a piece streams (32 x d x 2 x elem per
-// 32 keys), and >= 256 keys.
 //  - At least as many streams as slots: pieces of at most kMaxPiece keys
-//    (above), dispatched longest first.
+//    (above) and at least 40 * rows, so that the fp32 partials (rows x d x 4
+//    bytes, written once and read once by the combine) stay a few percent of
+//    the K/V bytes a piece streams; dispatched longest first, the items past
+//    the first round claimed at run time.
 //  - Fewer streams than slots: every work-group takes exactly one item (a
 //    second, nearly empty round of items ran 7-27% slower), and the pieces
 //    are cut so that the longest is as short as the slots allow: one piece
 //    per stream to start with, then repeatedly one more piece for the
 //    request whose pieces are currently longest, while its streams' extra
 //    items still fit the slots.  Every work-group streams at about the same
-//    rate, so the longest piece sets the kernel's end.
-#ifndef SV_MIN_PIECE_ROWS
-#define SV_MIN_PIECE_ROWS 40
-#endif
+//    rate, so the longest piece sets the kernel's end; the slots would
+//    otherwise idle, so pieces may be as short as 128 bytes per column (64
+//    bf16 keys) and 2 * rows keys.  Shorter ones lose to their partials and
+//    start-up: one request of 1000 keys x 8 KV heads (20 rows) 32-key pieces
+//    16.3 us, 64 14.8, 128 16.0, 256 19, whole 33.9; 4000 keys at 72 rows:
+//    64-key pieces 24.1, 128-256 21.3-21.9, 512 25.6, 2000 109.  Where no
+//    stream is longer than 512 bytes per column (256 bf16 keys) the combine
+//    launch costs more than a cut saves (205 keys: whole 13.6, cut 14.4; 300
+//    keys: whole 16.6, cut 14.9).
+// `coarse` (a caller's fixed scratch is too small for this): pieces of at
+// least 40 * rows and 256 keys.
 std::vector<int> piece_lengths(const std::vector<int>& len, const std::vector<int>& mult, int rows_max, int elem,
                                int64_t slots, bool coarse) {
   slots = std::max<int64_t>(slots, 1);
-  int64_t lo = std::max<int64_t>(SV_MIN_PIECE_ROWS * 2 / (coarse ? 2 : elem) * (int64_t)rows_max, 256);
-  lo = std::min<int64_t>((lo + 31) / 32 * 32, kMaxSplit);
   const size_t B = len.size();
   std::vector<int> out(B);
   int64_t streams = 0;
   for (size_t i = 0; i < B; ++i) streams += mult[i];
   if (streams >= slots) {
-    for (size_t i = 0; i < B; ++i) out[i] = piece_len(len[i], std::max(kMaxPiece, lo));
+    for (size_t i = 0; i < B; ++i) out[i] = piece_len(len[i], std::max(kMaxPiece, 40 * (int64_t)rows_max));
     return out;
   }
+  const int longest = *std::max_element(len.begin(), len.end());
+  if (!coarse && (int64_t)longest * elem <= 512) {
+    for (size_t i = 0; i < B; ++i) out[i] = piece_len(len[i], kMaxSplit);
+    return out;
+  }
+  int64_t lo = coarse ? std::max<int64_t>(40 * (int64_t)rows_max, 256)
+                      : std::max<int64_t>(2 * (int64_t)rows_max, 128 / elem);
+  lo = std::min<int64_t>((lo + 31) / 32 * 32, kMaxSplit);
   // greedy: a max-heap of (current piece length, request)
   std::vector<int64_t> n(B, 1);
   auto cur = [&](size_t i) { return ((int64_t)len[i] + n[i] - 1) / n[i]; };
@@ -424,6 +428,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
     const bool bf = attn->dtype == SPEC_BF16;
     const int D = attn->head_dim;
     const int Hq = attn->num_q_heads, Hkv = attn->num_kv_heads, G = Hq / Hkv;
+    P.kv_bytes = 2 * P.Nkv * Hkv * D * elem;
     const int rmax = sv::max_rows_per_item(P.layout);
     // query-head groups per request so that heads * n_i <= rmax
     std::vector<int> groups(P.B), hpg(P.B), len(P.B), mult(P.B);
@@ -448,7 +453,8 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
     }
     P.split = 0;
     for (int i = 0; i < P.B; ++i) P.split = std::max(P.split, plen[i]);
-    int64_t part = 0;
+    int64_t part = 0, streams = 0;
+    for (int i = 0; i < P.B; ++i) streams += mult[i];
     int nr = 1;
     {
       int64_t n_items = 0;
@@ -535,7 +541,8 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
         blk = std::max<int64_t>(blk, (int64_t)q.nseg * q.nq * Hq * D * 4);
         stream_bytes = std::max<int64_t>(stream_bytes, rows * q.nseg * D * 4);
       }
-      P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) && stream_bytes <= fuse_max_bytes();
+      P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) && 
+                stream_bytes <= fuse_max_bytes(attn->split_kv > 0 || streams >= slots ? kFuseMaxBytes : 0);
     }
   }
 
@@ -593,6 +600,14 @@ struct SideStream {
   hipEvent_t fork = nullptr, join = nullptr;
   bool ready = false;
 };
+// Below this many K/V bytes a step stays on the caller's stream: the fork and
+// join (event packets both queues wait on, and their host calls) cost more
+// than hiding the acceptance under so short an attention saves.  Steps over
+// 512-2048-key contexts, 8 KV heads, one stream against two: 1 request 31
+// against 45-55 us, 4 requests 36 against 50-60, 16 requests (88 MB of K/V)
+// 48 against 58-62, 32 requests (173 MB) 66 against 55-59; 1 request at 32 KV
+// heads 32 against 44-58.
+constexpr int64_t kOverlapMinBytes = 128 << 20;
 constexpr int kMaxDevices = 64;
 SideStream g_side[kMaxDevices];
 
@@ -878,10 +893,7 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
     return true;
   };
 
-#ifndef SV_OVERLAP
-#define SV_OVERLAP 1
-#endif
-  if (SV_OVERLAP && mode.overlap && attn && acc) {
+  if (mode.overlap && attn && acc && P.kv_bytes > kOverlapMinBytes) {
     SideStream* S = side_stream();
     if (!S) return SPEC_ERR_HIP;
     std::lock_guard<std::mutex> lk(S->mu);

@@ -28,13 +28,13 @@ CASES = [
 ]
 
 
-def _reference_and_bound(pool):
+def reference_and_bound(pool, p_rel=0.0):
     """fp64 output and, per row, a first-order bound of an fp32 evaluation:
     scores off by (d + 4) u scale sum|q k|, the exponentials by twice that
     (numerator and denominator) plus their own and the running sums' roundings,
-    (L + 16) u of sum p |v|."""
+    (L + 16) u of sum p |v|, plus p_rel of it (a rounding of p itself)."""
     def t(x):
-        return torch.from_numpy(np.asarray(x, np.float64))
+        return torch.from_numpy(W.as_f32(x, pool.qkv_dtype).astype(np.float64))
     Hq, Hkv, d = pool.num_q_heads, pool.num_kv_heads, pool.head_dim
     q, k, v = t(pool.q), t(pool.k), t(pool.v)
     ref, bound = torch.empty(q.shape, dtype=torch.float64), torch.empty(q.shape, dtype=torch.float64)
@@ -53,7 +53,7 @@ def _reference_and_bound(pool):
             ds = ((qq.abs() @ kk.abs().T) / d ** 0.5 * (d + 4) * UNIT).masked_fill(~see, 0).max(-1).values
             p = torch.softmax(s.masked_fill(~see, -np.inf), -1)
             ref[q0:q0 + n, h] = p @ vv
-            bound[q0:q0 + n, h] = (2 * ds[:, None] + (c + n + 16) * UNIT) * (p @ vv.abs())
+            bound[q0:q0 + n, h] = (2 * ds[:, None] + (c + n + 16) * UNIT + p_rel) * (p @ vv.abs())
     return ref.numpy(), bound.numpy()
 
 
@@ -62,7 +62,7 @@ def test_f32_attention(gpu_lib, name, kw, split):
     print(f"[f32] {name}", flush=True)
     pool = U.custom_pool(**kw, qkv=W.F32, seed=U.case_seed(name))
     b = DeviceBatch(pool, "cuda")
-    ref, bound = _reference_and_bound(pool)
+    ref, bound = reference_and_bound(pool)
     for pad in (0, 4):
         v = Verifier(b, split_kv=split)
         if pad:                      # token rows and heads with gaps between them

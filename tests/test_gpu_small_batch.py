@@ -1,0 +1,90 @@
+"""Batches of fewer streams than the device has slots: the plan cuts them into
+short pieces and a separate combine follows, and small steps stay on the
+caller's stream.  Attention against fp64 within a derived bound at the rule's
+edges (streams just under and over its shortest cut, one to five waves, more
+pieces than the combine takes in one pass), the whole step against the
+attention and acceptance calls alone on both sides of the stream rule, and the
+no-allocation call's coarser plan."""
+import numpy as np
+import pytest
+import torch
+
+import parity_util as U
+from paper_2505_17074_amd import binding as B
+from paper_2505_17074_amd import workload as W
+from paper_2505_17074_amd.batch import DeviceBatch, PagedKV, Verifier
+from test_gpu_f32_attn import reference_and_bound
+
+# bf16 probabilities are carried in two bf16 parts (a relative 2^-17)
+P_REL = 2.0 ** -17
+CASES = [
+    ("uncut_256", dict(ctx=[251, 3], k=[4, 4], Hq=4, Hkv=4)),
+    ("cut_257", dict(ctx=[252, 3], k=[4, 4], Hq=4, Hkv=4)),
+    ("k0_one_row", dict(ctx=[700], k=[0], Hq=2, Hkv=2)),
+    ("two_waves", dict(ctx=[1000], k=[4], Hq=8, Hkv=2)),
+    ("three_waves_d64", dict(ctx=[515, 65], k=[8, 2], Hq=8, Hkv=2, d=64)),
+    ("four_waves_tree", dict(ctx=[2000], tree_parent=W.full_binary_tree_parents(2, 4), Hq=8, Hkv=2)),
+    ("five_waves", dict(ctx=[1500, 90], k=[8, 8], Hq=16, Hkv=2)),
+    ("many_pieces", dict(ctx=[34000], k=[2], Hq=4, Hkv=1)),
+    ("f32_uncut_128", dict(ctx=[123], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
+    ("f32_cut_129", dict(ctx=[124], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,kw", CASES, ids=[c[0] for c in CASES])
+def test_short_pieces(gpu_lib, name, kw):
+    print(f"[small] {name}", flush=True)
+    pool = U.custom_pool(**kw, seed=U.case_seed(name))
+    b = DeviceBatch(pool, "cuda")
+    f32 = pool.qkv_dtype == W.F32
+    ref, bound = reference_and_bound(pool, 0.0 if f32 else P_REL)
+    v = Verifier(b)
+    b.out.fill_(float("nan"))
+    v.run("attn")
+    out = v.results()["out"]
+    assert (np.abs(out - ref) <= bound).all(), float((np.abs(out - ref) / bound).max())
+    if not f32:
+        b.out.fill_(float("nan"))
+        pk = PagedKV(b, 32)              # holds the page pools while they are read
+        paged = Verifier(b, attn=pk.attn_args())
+        paged.run("attn")
+        assert np.array_equal(paged.results()["out"], out)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ctx", [4000, 4200])       # 125 and 131 MiB of K/V: one stream, two streams
+def test_step_on_one_or_two_streams(gpu_lib, ctx):
+    print(f"[small] step ctx {ctx}", flush=True)
+    pool = U.custom_pool(ctx=[ctx] * 8, k=[3] * 8, Hq=8, Hkv=8, V=5000, seed=5)
+    b = DeviceBatch(pool, "cuda")
+    v = Verifier(b)
+    v.run("attn")
+    v.run("accept")
+    want = v.results()
+    for t in (b.out, b.accepted_len, b.next_token, b.accepted_node):
+        t.zero_()
+    v.run("verify")
+    got = v.results()
+    for key in want:
+        assert np.array_equal(want[key], got[key]), key
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="made-up device pointers: only where nothing can be launched")
+def test_noalloc_plans_coarser_before_it_refuses():
+    """A step whose automatic split needs more than the static scratch, and
+    whose longer pieces fit it, is not refused for its size."""
+    n, k = 100, 9
+    req = B.make_requests(np.full(n, 3000), np.full(n, k))
+    a = B.SpecAttnArgs()
+    a.num_q_heads, a.num_kv_heads, a.head_dim, a.dtype = 8, 1, 128, B.SPEC_BF16
+    a.q = a.k = a.v = a.out = 1 << 20
+    a.q_stride_tok, a.q_stride_head, a.kv_stride_tok, a.kv_stride_head = 1024, 128, 128, 128
+    c = B.SpecAcceptArgs()
+    c.vocab, c.dtype = 4000000, B.SPEC_F32
+    c.target_logits = c.draft_probs = c.draft_tokens = c.uniforms = 1 << 20
+    c.accepted_len = c.next_token = 1 << 20
+    c.logits_stride = c.probs_stride = c.vocab
+    st, dev, _ = B.spec_workspace_bytes(req, a, c)
+    assert st == B.SPEC_OK and dev > B.SPEC_NOALLOC_SCRATCH_BYTES
+    assert B.spec_verify_noalloc(req, a, c, 0) == B.SPEC_ERR_HIP        # past the size check, no device here
