@@ -377,7 +377,7 @@ SPEC_API spec_status_t spec_verify_noalloc(const spec_requests_t* req,
  * the logits once into acc->target_logits (an OUTPUT here: [Nq, vocab] in
  * acc->dtype, fp32 or rounded to bf16, row stride acc->logits_stride) and,
  * in its epilogue, the maximum and the sum of exp(l - max) of every
- * (row, 256-entry tile) of the stored logits; the acceptance then folds those
+ * (row, vocabulary tile) of the stored logits; the acceptance then folds those
  * into its normalisers instead of streaming the logits again, and reads the
  * logits only for its tests and the final sample.  Results equal spec_accept
  * on the same logits except where u * S lies within rounding of a boundary

@@ -27,6 +27,7 @@
 // lies within ~1e-8 (probability mass) of a cumulative boundary.
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "sv_internal.h"
 
@@ -349,8 +350,9 @@ __device__ __forceinline__ double load_dev(const double* p) {
 // build, so the verify path keeps the smaller register footprint (80 VGPRs
 // against 96 with the tile fold's held loads: 6 waves per SIMD instead of 5
 // beside the attention).
-template <typename T, bool TILES>
+template <typename T, int HELD>
 __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
+  constexpr bool TILES = HELD > 0;
   __shared__ double redd[4];
   __shared__ float redf[4];
   __shared__ float s_M[kMaxNodes];
@@ -400,7 +402,7 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
   // A row of at most 64 * kHeld tile statistics is loaded whole into
   // registers before any is used (one round trip); chunk statistics (at
   // most a few per lane) and longer rows take two passes.
-  constexpr int kHeld = 8;
+  constexpr int kHeld = TILES ? HELD : 1;
   const int nst = TILES ? p.ntiles : p.nch;
   for (int r = wv; r < N; r += kAccThreads / 64) {
     if (p.tree == 1 && !p.all_stats && p.topo.qrank[r] < 0) continue;     // a leaf's row: none yet
@@ -548,8 +550,8 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
       // after the LM head: each chunk's statistics folded from its tiles,
       // one tile per thread and a chunk's tiles on consecutive lanes; kQ
       // tiles per thread are loaded before any is used
-      static_assert(kLmhTilesPerChunk <= 64 && (kLmhTilesPerChunk & (kLmhTilesPerChunk - 1)) == 0,
-                    "a chunk's tiles fold inside one wave");
+      static_assert(kAccChunk / kLmhNTLow <= 64, "a chunk's tiles (a power of two) fold inside one wave");
+      const int tpc = p.tpc;
       constexpr int kQ = 4;
       const ChunkStat* ts = p.tiles + (int64_t)d.row * p.ntiles;
       for (int j0 = 0; j0 < p.ntiles; j0 += kQ * kAccThreads) {
@@ -569,11 +571,11 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
         for (int q = 0; q < kQ; ++q) {
           const int j = j0 + q * kAccThreads + tid;
           float m = tm[q];
-          for (int o = kLmhTilesPerChunk / 2; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+          for (int o = tpc / 2; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
           double sum = j < p.ntiles ? tsm[q] * exp((double)tm[q] - (double)m) : 0.0;
-          for (int o = kLmhTilesPerChunk / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
-          const int k = j / kLmhTilesPerChunk;
-          if (j % kLmhTilesPerChunk == 0 && k < p.nch) {
+          for (int o = tpc / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+          const int k = j / tpc;
+          if (j % tpc == 0 && k < p.nch) {
             s_mass[k] = sum;
             s_mc[k] = m;
           }
@@ -1167,13 +1169,14 @@ __global__ __launch_bounds__(kAccThreads) void acc_validate(AccParams p, uint32_
   if (bad) atomicOr(flag, bad);
 }
 
-// Chunk statistics from the LM head's tile statistics: thread t of the grid
-// folds the kLmhTilesPerChunk tiles of one (row, chunk) in tile order into
-// (max, sum of exp(l - max)), max over the tiles' maxima and the tiles' sums
-// rescaled in fp64.  The first B work-groups also make the device copies of
+// Chunk statistics from the LM head's tile statistics: tpc consecutive lanes
+// fold the tpc tiles of one (row, chunk), one each, into (max, sum of exp(l -
+// max)): the tiles' sums rescaled in fp64 and added by an xor butterfly.  One
+// round trip for a chunk's tiles (one thread walking 16 or 32 of them took 5
+// us longer).  The first B work-groups also make the device copies of
 // the request and node tables and clear the tickets, as the row-statistics
 // kernel does on the unfused path.
-__global__ __launch_bounds__(kAccThreads) void acc_foldstats(AccParams p, const ChunkStat* tiles, int ntiles) {
+__global__ __launch_bounds__(kAccThreads) void acc_foldstats(AccParams p, const ChunkStat* tiles, int ntiles, int tpc) {
   if (blockIdx.x < p.B) {
     if (threadIdx.x < 2)
       reinterpret_cast<uint4*>(p.reqs + blockIdx.x)[threadIdx.x] =
@@ -1183,24 +1186,24 @@ __global__ __launch_bounds__(kAccThreads) void acc_foldstats(AccParams p, const 
       for (int x = blockIdx.x * kAccThreads + threadIdx.x; x < p.nodes_n16; x += p.B * kAccThreads)
         reinterpret_cast<uint4*>(p.nodes)[x] = reinterpret_cast<const uint4*>(p.nodes_src)[x];
   }
-  const int64_t idx = (int64_t)blockIdx.x * kAccThreads + threadIdx.x;
-  if (idx >= (int64_t)p.Nq * p.nch) return;
-  const int row = (int)(idx / p.nch), c = (int)(idx % p.nch);
-  const int t0 = c * kLmhTilesPerChunk, t1 = min(t0 + kLmhTilesPerChunk, ntiles);
-  const ChunkStat* ts = tiles + (int64_t)row * ntiles;
-  float m = -INFINITY;
-  for (int t = t0; t < t1; ++t) m = fmaxf(m, ts[t].m);
-  double sum = 0.0;
-  for (int t = t0; t < t1; ++t) sum += ts[t].s * exp((double)ts[t].m - (double)m);
-  p.rowstats[idx] = ChunkStat{sum, m, 0.f};
+  const int64_t idx = ((int64_t)blockIdx.x * kAccThreads + threadIdx.x) / tpc;
+  if (idx >= (int64_t)p.Nq * p.nch) return;            // whole groups of tpc lanes
+  const int row = (int)(idx / p.nch), t = (int)(idx % p.nch) * tpc + (int)(threadIdx.x % tpc);
+  ChunkStat st{0.0, -INFINITY, 0.f};
+  if (t < ntiles) st = tiles[(int64_t)row * ntiles + t];
+  float m = st.m;
+  for (int o = tpc / 2; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  double sum = t < ntiles ? st.s * exp((double)st.m - (double)m) : 0.0;
+  for (int o = tpc / 2; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+  if (threadIdx.x % tpc == 0) p.rowstats[idx] = ChunkStat{sum, m, 0.f};
 }
 
 }  // namespace
 
-hipError_t launch_foldstats(const AccParams& p, const ChunkStat* tiles, int ntiles, hipStream_t s) {
-  const int64_t n = (int64_t)p.Nq * p.nch;
+hipError_t launch_foldstats(const AccParams& p, const ChunkStat* tiles, int ntiles, int tpc, hipStream_t s) {
+  const int64_t n = (int64_t)p.Nq * p.nch * tpc;
   const dim3 grid((unsigned)std::max<int64_t>((n + kAccThreads - 1) / kAccThreads, p.B));
-  acc_foldstats<<<grid, dim3(kAccThreads), 0, s>>>(p, tiles, ntiles);
+  acc_foldstats<<<grid, dim3(kAccThreads), 0, s>>>(p, tiles, ntiles, tpc);
   return hipGetLastError();
 }
 
@@ -1241,13 +1244,15 @@ hipError_t launch_decide(const AccParams& p, hipStream_t s) {
     return hipGetLastError();
   }
   const dim3 grid((unsigned)(p.B * p.nch));
-  if (p.tiles) {
-    if (p.bf16) acc_decide_select<uint16_t, true><<<grid, block, 0, s>>>(p);
-    else acc_decide_select<float, true><<<grid, block, 0, s>>>(p);
-  } else {
-    if (p.bf16) acc_decide_select<uint16_t, false><<<grid, block, 0, s>>>(p);
-    else acc_decide_select<float, false><<<grid, block, 0, s>>>(p);
-  }
+  auto launch = [&](auto held) {
+    constexpr int H = decltype(held)::value;
+    if (p.bf16) acc_decide_select<uint16_t, H><<<grid, block, 0, s>>>(p);
+    else acc_decide_select<float, H><<<grid, block, 0, s>>>(p);
+  };
+  if (!p.tiles) launch(std::integral_constant<int, 0>{});
+  else if (p.ntiles <= 256) launch(std::integral_constant<int, 4>{});
+  else if (p.ntiles <= 512) launch(std::integral_constant<int, 8>{});
+  else launch(std::integral_constant<int, 16>{});
   return hipGetLastError();
 }
 

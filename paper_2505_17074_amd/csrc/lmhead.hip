@@ -10,24 +10,28 @@
 // l % 16, k = 8 (l / 16) .. +7 of a 16-row block, for the A (hidden) and the
 // B (weight) operand alike, and holds C[4 (l / 16) + i][l % 16].
 //
-// A work-group (WR x WC = 4 x 2 waves, two per SIMD) computes a tile of
-// 16 RB WR rows x 256 vocabulary entries; wave (wr, wc) owns row blocks
-// RB wr .. RB wr + RB - 1 and column blocks CB wc .. CB wc + CB - 1 (CB =
-// 16 / WC), so each slice of k is read from LDS (RB + CB) times per wave
-// instead of once per row block and column block.  64-k slices of the hidden
-// rows and the weight rows (one 128-byte cache line per row) stream L2 ->
-// LDS through an NS-stage ring of direct buffer -> LDS transfers (the
-// attention kernel's ring); all of a slice's operands are read into
-// registers before its MFMAs.
+// 64-k slices of the hidden rows and the weight rows (one 128-byte cache line
+// per row) stream through LDS by direct buffer -> LDS transfers; the 16-byte
+// chunks of a row are swizzled so that the operand reads hit every bank.  Eight
+// waves, one work-group per CU.  Two kernels by M:
 //
-// What bounds it: every CU fetches its operand lines from L2 at a roughly
-// fixed rate (its vector L1 keeps a bounded number of misses in flight), so
-// the time goes with the cache lines a CU fetches per slice, hidden rows +
-// 256 weight rows, and with the rounds of work-groups over the CUs.  Tall
-// tiles fetch fewer lines per flop but fill the LDS with fewer ring stages;
-// lmh_geometry() picks the tile height per shape from that cost, and the row
-// tiles of one vocabulary tile run together on one XCD, so that each weight
-// line comes from HBM once and the hidden rows stay in L2.
+//  - lmh_low (M <= 192): every row against 128 vocabulary entries, a deep ring
+//    whose stream runs on from tile to tile.  Bound by the weights' stream:
+//    20 x 4096 x 32000 (262 MB) 41 us of GEMM, 72 x 8192 x 128256 (2.1 GB) 342
+//    us, 6.2-6.4 TB/s.  What it took over 256-entry tiles of 64 or 128 rows
+//    (59 and 395 us): all CUs busy on one vocabulary, the transfers' offsets
+//    out of the scalar unit (descriptors rebuilt per transfer held the ring at
+//    4.8 TB/s), each tile starting at another k slice (rows a power of two
+//    apart otherwise queue on the same channels: 425 -> 378 us), and the
+//    epilogue's reductions on the vector ALU (12 -> 5 us a tile).
+//  - lmh_tall: 64 RB rows x 256 entries (RB <= 6), 4 x 2 waves of 16 RB x 128.
+//    Bound by the matrix cores and by what a slice's hand-over leaves idle.  A
+//    wave keeps its RB hidden operands in registers over a half slice and
+//    passes the weight operands through two, so 384 x 256 fits 256 registers
+//    and 700 rows take one round of work-groups: 716 x 4096 x 32000 160 us
+//    (1.17 PFLOP/s; the products alone, without transfers, 120) against 202
+//    for two rounds of 192-row tiles whose operands were read a slice at a
+//    time; 92 MB of logits take 15 us of the epilogue.
 #include "sv_internal.h"
 
 #include <algorithm>
@@ -36,37 +40,20 @@
 namespace sv {
 namespace {
 
+#ifndef SV_LMH_LOW_NS
+#define SV_LMH_LOW_NS 8
+#endif
+#ifndef SV_LMH_W_CPOL
+#define SV_LMH_W_CPOL 2
+#endif
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-#ifndef SV_LMH_KS
-#define SV_LMH_KS 2
-#endif
-#ifndef SV_LMH_HOIST
-#define SV_LMH_HOIST 1
-#endif
-constexpr int kKS = SV_LMH_KS;       // 32-k halves per slice
-constexpr int kRowB = 64 * kKS;      // bytes of one row slice in LDS
-static_assert(kKS == 1 || kKS == 2, "32- or 64-k slices");
-#ifndef SV_LMH_WR
-#define SV_LMH_WR 4
-#endif
-#ifndef SV_LMH_WC
-#define SV_LMH_WC 2
-#endif
-#ifndef SV_LMH_MAXRB
-#define SV_LMH_MAXRB 4
-#endif
-#ifndef SV_LMH_MAXNS
-#define SV_LMH_MAXNS 4
-#endif
-constexpr int kWR = SV_LMH_WR;       // waves along the rows
-constexpr int kWC = SV_LMH_WC;       // waves along the vocabulary tile
-constexpr int kLmhWaves = kWR * kWC;
-constexpr int kLmhThreads = 64 * kLmhWaves;
-constexpr int kCB = kLmhNT / (16 * kWC);   // 16-column blocks per wave
-static_assert(kCB * 16 * kWC == kLmhNT, "the waves' column blocks tile the vocabulary tile");
+constexpr int kWaves = 8;                 // two per SIMD, one work-group per compute unit
+constexpr int kThreads = 64 * kWaves;
+constexpr int kRowB = 128;                // bytes of one row's 64-k slice
+constexpr int kLdsBytes = 160 * 1024;
 
 template <int N>
 __device__ __forceinline__ void lmh_wait_vm() {
@@ -75,198 +62,148 @@ __device__ __forceinline__ void lmh_wait_vm() {
 }
 __device__ __forceinline__ void lmh_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// 16-byte chunk c of LDS row r sits at chunk c ^ swz(r): the 8 rows that 8
-// consecutive lanes read (one chunk each) cover all 32 banks (128-byte rows:
-// one row per bank sweep; 64-byte rows: two).
-__device__ __forceinline__ int lmh_swz(int r) { return kKS == 2 ? (r & 7) : ((r >> 1) & 3); }
+// 16-byte chunk c of LDS row r sits at chunk c ^ (r & 7): the 8 rows that 8
+// consecutive lanes read (one chunk each) cover all the banks.
+__device__ __forceinline__ int lmh_swz(int r) { return r & 7; }
 
-template <int RB>
-struct LmhGeo {
-  static constexpr int RA = 16 * RB * kWR;            // hidden rows per tile
-  static constexpr int ROWS = RA + kLmhNT;            // LDS rows per stage
-  static constexpr int STAGE = ROWS * kRowB;
-  static constexpr int XF = ROWS * kRowB / 1024;      // 1 KB transfers per stage
-  static constexpr int PER = (XF + kLmhWaves - 1) / kLmhWaves;   // per wave (padded with repeats)
-  // ring depth: as many stages as 144 KB of LDS holds, at most SV_LMH_MAXNS
-  static constexpr int FIT = (144 * 1024) / STAGE;
-  static constexpr int NS = FIT < SV_LMH_MAXNS ? FIT : SV_LMH_MAXNS;
-  static_assert(NS >= 2, "two stages at least");
-};
-
-template <int RB, bool BF16OUT>
-// one work-group per CU (its ring fills the LDS): 8 waves are 2 per SIMD
-__global__ __launch_bounds__(kLmhThreads) __attribute__((amdgpu_waves_per_eu(kLmhWaves / 4, kLmhWaves / 4))) void lmh_gemm(LmhParams p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  using G = LmhGeo<RB>;
-  constexpr int PER = G::PER, NS = G::NS, CB = kCB;
-  __shared__ __attribute__((aligned(1024))) char lds[NS * G::STAGE];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wr = w / kWC, wc = w % kWC;
-  const int l16 = lane & 15, grp = lane >> 4;
-
-  // block -> (row tile, vocabulary tile): the row tiles of one vocabulary
-  // tile are 8 blocks apart (one XCD of the round-robin dispatch) and within
-  // one window of 8 * m_tiles blocks, so they run together and share that
-  // tile's weight rows in the XCD's L2
-  // the decision kernel's inputs the row-statistics kernel would otherwise
-  // prepare (every work-group may take part; the grid can be smaller than B)
+// The decision kernel's inputs the row-statistics kernel would otherwise
+// prepare (every work-group may take part; the grid can be smaller than B).
+__device__ __forceinline__ void lmh_setup(const LmhParams& p) {
   for (int b = blockIdx.x; b < p.B; b += gridDim.x) {
     if (threadIdx.x < 2)
       reinterpret_cast<uint4*>(p.reqs + b)[threadIdx.x] = reinterpret_cast<const uint4*>(p.reqs_src + b)[threadIdx.x];
     if (threadIdx.x == 0) p.tickets[b] = 0;
   }
-  for (int x = blockIdx.x * kLmhThreads + threadIdx.x; x < p.nodes_n16; x += gridDim.x * kLmhThreads)
+  for (int x = blockIdx.x * kThreads + threadIdx.x; x < p.nodes_n16; x += gridDim.x * kThreads)
     reinterpret_cast<uint4*>(p.nodes)[x] = reinterpret_cast<const uint4*>(p.nodes_src)[x];
+}
+
+// Tile `item` of the launch: the row tiles of one vocabulary tile are 8 items
+// apart (one XCD of the round-robin dispatch) and within one window of 8 *
+// m_tiles items, so they run together and share that tile's weight rows in
+// the XCD's L2.
+struct LmhTile {
+  int m0, mrows, nt, n0, ncols;
+};
+template <int NT>
+__device__ __forceinline__ LmhTile lmh_tile(const LmhParams& p, int item) {
   const int T = p.m_tiles;
-  const int g = blockIdx.x / (8 * T), r8 = blockIdx.x % (8 * T);
-  const int mt = r8 / 8, nt = g * 8 + (r8 % 8);
-  if (nt >= p.ntiles) return;                       // uniform: past the vocabulary
-  const int m0 = mt * p.tile_rows, n0 = nt * kLmhNT;
-  const int mrows = min(p.tile_rows, p.M - m0), ncols = min(kLmhNT, p.V - n0);
-  if (mrows <= 0) return;
-  // buffer resources over this tile's rows: loads past them read zeros
-  const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.hidden + (int64_t)m0 * p.h_st), 0, (uint32_t)(mrows * p.h_st * 2), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.weight + (int64_t)n0 * p.w_st), 0, (uint32_t)(ncols * p.w_st * 2), 0x00020000);
-  // this lane's byte offset in each of its transfers (the k slice's start is
-  // soffset): transfer j fills 1 KB of LDS rows from row (1024 / kRowB) j on,
-  // lane l the 16 bytes at LDS chunk l % (kRowB / 16) of row (1024 / kRowB) j
-  // + l / (kRowB / 16)
-  uint32_t off[PER];
-  bool isw[PER];
-  int dst[PER];
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int j = (w + kLmhWaves * q) % G::XF;       // transfer index (repeats pad the last waves)
-    constexpr int CPR = kRowB / 16;                  // chunks per row
-    const int row = (1024 / kRowB) * j + lane / CPR; // LDS row of this lane's chunk
-    const int chunk = (lane % CPR) ^ lmh_swz(row);   // global chunk that lands at LDS chunk lane % CPR
-    isw[q] = row >= G::RA;
-    const int grow = isw[q] ? row - G::RA : row;
-    off[q] = (uint32_t)grow * (uint32_t)((isw[q] ? p.w_st : p.h_st) * 2) + (uint32_t)chunk * 16u;
-    dst[q] = j * 1024;
-  }
-  auto issue = [&](int stage, int t) {
-    char* base = lds + stage * G::STAGE;
-    const uint32_t soff = (uint32_t)t * kRowB;        // 32 kKS bf16 of k per slice
-#pragma unroll
-    for (int q = 0; q < PER; ++q)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(isw[q] ? rw : rh, (lds_void_t*)(base + dst[q]), 16, off[q], soff, 0,
-                                               0);
-  };
+  const int g = item / (8 * T), r8 = item % (8 * T);
+  LmhTile t;
+  t.nt = g * 8 + r8 % 8;
+  t.m0 = (r8 / 8) * p.tile_rows;
+  t.n0 = t.nt * NT;
+  t.mrows = min(p.tile_rows, p.M - t.m0);
+  t.ncols = min(NT, p.V - t.n0);          // <= 0 past the vocabulary
+  return t;
+}
 
-  f32x4 acc[RB][CB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // LDS read offsets in a stage: a 16-row block starts at a multiple of 16,
-  // so swz(row) = swz(l16) and the chunk of k half h is (4 h + grp) ^ swz(l16)
-  uint32_t ch[kKS];
-#pragma unroll
-  for (int h = 0; h < kKS; ++h) ch[h] = (uint32_t)(((4 * h + grp) ^ lmh_swz(l16)) * 16);
-  const uint32_t abase = (uint32_t)(16 * RB * wr + l16) * kRowB;
-  const uint32_t bbase = (uint32_t)(G::RA + 16 * CB * wc + l16) * kRowB;
-
-  const int nk = (p.K + 32 * kKS - 1) / (32 * kKS);
-  const int nfull = p.K / (32 * kKS);               // 64-k slices, K % 64 == 32: the last one holds 32 k only
-#pragma unroll
-  for (int st = 0; st < NS - 1; ++st)
-    if (st < nk) issue(st, st);
-  auto slice = [&](int t, auto full_c) {
-    constexpr bool FULL = decltype(full_c)::value;
-    const int stage = t % NS;
-    // this wave's transfers of slice t have landed (later ones may still fly)
-    if (t + NS - 2 < nk) lmh_wait_vm<PER * (NS - 2)>();
-    else lmh_wait_vm<0>();
-    lmh_barrier();                  // everyone's have; stage (t - 1) % NS is free
-    if (t + NS - 1 < nk) issue((t + NS - 1) % NS, t + NS - 1);
-    const char* sb = lds + stage * G::STAGE;
-    constexpr int NH = FULL ? kKS : 1;
-    bf16x8 a[kKS][RB], b[kKS][CB];
-    auto rd = [&](int h) {
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) b[h][cb] = *reinterpret_cast<const bf16x8*>(sb + bbase + cb * 16 * kRowB + ch[h]);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) a[h][rb] = *reinterpret_cast<const bf16x8*>(sb + abase + rb * 16 * kRowB + ch[h]);
-    };
-    auto mm = [&](int h) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[h][rb], b[h][cb], acc[rb][cb], 0, 0, 0);
-    };
-#if SV_LMH_HOIST
-    // every read of the slice is issued before its first MFMA
-#pragma unroll
-    for (int h = 0; h < NH; ++h) rd(h);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int h = 0; h < NH; ++h) mm(h);
-#else
-    // one 32-k half at a time: its operands into registers, then its MFMAs
-    // (the other wave on the SIMD covers the reads' latency)
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      rd(h);
-      __builtin_amdgcn_sched_barrier(0);
-      mm(h);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+#ifndef SV_LMH_STAG
+#define SV_LMH_STAG 5
 #endif
-  };
-  for (int t = 0; t < nfull; ++t) slice(t, std::true_type{});
-  if (nk > nfull) slice(nfull, std::false_type{});
-  lmh_wait_vm<0>();
-  __syncthreads();                  // the ring is no longer read: reuse its LDS
+__device__ __forceinline__ int lmh_first_slice(const LmhParams& p, int nt, int nk) {
+  return p.K % 64 == 0 ? (nt * SV_LMH_STAG) % nk : 0;
+}
+// Buffer over `rows` rows of K bf16 at stride st elements, ending with the last
+// row's last element: loads past it (rows of a partial tile, the second half
+// of a K % 64 == 32 tail in the last row) read zeros.  The k offset goes into
+// the vector offset, which the bounds check covers.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t lmh_rows(const uint16_t* src, int rows, int64_t st, int K) {
+  const int64_t bytes = rows > 0 ? ((int64_t)(rows - 1) * st + K) * 2 : 0;
+  return __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, (uint32_t)bytes, 0x00020000);
+}
 
-  // Epilogue.  The logits are stored (fp32, or rounded to bf16), and the
-  // statistics of each row over the tile's 256 entries are taken on the
-  // stored values: the maximum, then the sum of exp(l - max) in fp64, lane
-  // sums in column-block order, then across the 16 lanes of a row by an xor
-  // butterfly, then across the WC waves of the row in wave order.
-  float* red_m = reinterpret_cast<float*>(lds);                      // [WC][RA]
-  double* red_s = reinterpret_cast<double*>(lds + kWC * G::RA * 4);  // [WC][RA]
-  float val[RB][CB][4];
+// Reductions over the 16 lanes of a DPP row (all of them get the result): the
+// pairs, the quads, then quad against quad and half against half by
+// mirroring, which hold uniform values by then.  On the vector ALU: the LDS
+// shuffles they replace took most of the epilogue (see lmh_epilogue).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  const int v = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const unsigned long long v = __builtin_bit_cast(unsigned long long, x);
+  const int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
+  const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, true);
+  const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)h << 32) | l);
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+__device__ __forceinline__ float max16(float x) {
+  x = fmaxf(x, dpp<kXor1>(x));
+  x = fmaxf(x, dpp<kXor2>(x));
+  x = fmaxf(x, dpp<kHalfMirror>(x));
+  return fmaxf(x, dpp<kMirror>(x));
+}
+__device__ __forceinline__ double sum16(double x) {
+  x += dpp<kXor1>(x);
+  x += dpp<kXor2>(x);
+  x += dpp<kHalfMirror>(x);
+  return x + dpp<kMirror>(x);
+}
+
+// Epilogue of one tile.  The logits are stored (fp32, or rounded to bf16),
+// and the statistics of each row over the tile's NT entries are taken on the
+// stored values: the maximum, then the sum of exp(l - max) in fp64, lane
+// sums in column-block order, then across the 16 lanes of a row, then across the WC waves of the row in wave order.  `red` holds
+// WC * RA * 12 bytes of LDS that nothing else reads or writes meanwhile.
+template <int RB, int CB, int WR, int WC, bool BF16OUT>
+__device__ __forceinline__ void lmh_epilogue(const LmhParams& p, const LmhTile& t, f32x4 (&acc)[RB][CB], char* red,
+                                             int wr, int wc, int lane) {
+  constexpr int RA = 16 * RB * WR, NT = 16 * CB * WC;
+  const int l16 = lane & 15, grp = lane >> 4;
+  double* red_s = reinterpret_cast<double*>(red);                    // [WC][RA]
+  float* red_m = reinterpret_cast<float*>(red + WC * RA * 8);        // [WC][RA]
+  using OT = typename std::conditional<BF16OUT, uint16_t, float>::type;
+  // this lane's byte offset from a row block's first row and column
+  const int64_t lane_off = ((int64_t)(4 * grp) * p.o_st + 16 * CB * wc + l16) * (int64_t)sizeof(OT);
+  const bool narrow = (13 * p.o_st + NT) * (int64_t)sizeof(OT) <= 0x7fffffff;   // uniform: 32-bit lane offsets
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row0 = 16 * (RB * wr + rb);
+    const bool whole = narrow && t.ncols == NT && row0 + 16 <= t.mrows;          // wave-uniform
+    OT* base = static_cast<OT*>(p.out) + (int64_t)(t.m0 + row0) * p.o_st + t.n0;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       const int col = 16 * CB * wc + 16 * cb + l16;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row = 16 * (RB * wr + rb) + 4 * grp + i;
         float v = acc[rb][cb][i];
+        OT st;
         if constexpr (BF16OUT) {
           const uint32_t u = __float_as_uint(v);
-          const uint16_t b = (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);   // round to nearest even
-          v = __uint_as_float((uint32_t)b << 16);
-          if (row < mrows && col < ncols)
-            static_cast<uint16_t*>(p.out)[(int64_t)(m0 + row) * p.o_st + n0 + col] = b;
+          st = (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);   // round to nearest even
+          v = __uint_as_float((uint32_t)st << 16);
         } else {
-          if (row < mrows && col < ncols) static_cast<float*>(p.out)[(int64_t)(m0 + row) * p.o_st + n0 + col] = v;
+          st = v;
         }
-        val[rb][cb][i] = col < ncols ? v : -INFINITY;
+        if (whole)
+          *reinterpret_cast<OT*>(reinterpret_cast<char*>(base + i * p.o_st + 16 * cb) + (uint32_t)lane_off) = st;
+        else if (row0 + 4 * grp + i < t.mrows && col < t.ncols)
+          base[(int64_t)(4 * grp + i) * p.o_st + col] = st;
+        acc[rb][cb][i] = col < t.ncols ? v : -INFINITY;
       }
     }
+    __builtin_amdgcn_sched_barrier(0);   // one row block at a time: bounded registers
+  }
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float m = val[rb][0][i];
+      float m = acc[rb][0][i];
 #pragma unroll
-      for (int cb = 1; cb < CB; ++cb) m = fmaxf(m, val[rb][cb][i]);
-      for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
-      if (l16 == 0) red_m[wc * G::RA + 16 * (RB * wr + rb) + 4 * grp + i] = m;
+      for (int cb = 1; cb < CB; ++cb) m = fmaxf(m, acc[rb][cb][i]);
+      m = max16(m);
+      if (l16 == 0) red_m[wc * RA + 16 * (RB * wr + rb) + 4 * grp + i] = m;
+      if (i == 3) __builtin_amdgcn_sched_barrier(0);
     }
-  __syncthreads();
+  lmh_barrier();
   auto row_max = [&](int row) {
     float m = red_m[row];
 #pragma unroll
-    for (int x = 1; x < kWC; ++x) m = fmaxf(m, red_m[x * G::RA + row]);
+    for (int x = 1; x < WC; ++x) m = fmaxf(m, red_m[x * RA + row]);
     return m;
   };
 #pragma unroll
@@ -277,72 +214,378 @@ __global__ __launch_bounds__(kLmhThreads) __attribute__((amdgpu_waves_per_eu(kLm
       const float m = row_max(row);
       double sm = 0.0;
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) sm += (double)exp_rel(val[rb][cb][i], m);
-      for (int o = 1; o < 16; o <<= 1) sm += __shfl_xor(sm, o);
-      if (l16 == 0) red_s[wc * G::RA + row] = sm;
+      for (int cb = 0; cb < CB; ++cb) sm += (double)exp_rel(acc[rb][cb][i], m);
+      sm = sum16(sm);
+      if (l16 == 0) red_s[wc * RA + row] = sm;
+      if (i == 3) __builtin_amdgcn_sched_barrier(0);
     }
-  __syncthreads();
-  for (int row = threadIdx.x; row < mrows; row += kLmhThreads) {
+  lmh_barrier();
+  for (int row = threadIdx.x; row < t.mrows; row += kThreads) {
     double sm = red_s[row];
 #pragma unroll
-    for (int x = 1; x < kWC; ++x) sm += red_s[x * G::RA + row];
-    p.tiles[(int64_t)(m0 + row) * p.ntiles + nt] = ChunkStat{sm, row_max(row), 0.f};
+    for (int x = 1; x < WC; ++x) sm += red_s[x * RA + row];
+    p.tiles[(int64_t)(t.m0 + row) * p.ntiles + t.nt] = ChunkStat{sm, row_max(row), 0.f};
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Low tiles: all of up to 192 rows x 128 vocabulary entries.
+// ---------------------------------------------------------------------------
+template <int RB, int WR>
+struct LowGeo {
+  static constexpr int WC = kWaves / WR, NT = kLmhNTLow, CB = NT / (16 * WC);
+  static constexpr int RA = 16 * RB * WR;             // hidden rows
+  static constexpr int STAGE = (RA + NT) * kRowB;
+  static constexpr int RED = WC * RA * 12;
+  static constexpr int FIT = (kLdsBytes - RED) / STAGE;
+  static constexpr int NS = FIT < SV_LMH_LOW_NS ? FIT : SV_LMH_LOW_NS;   // ring stages
+  static constexpr int XH = RA / 8;                   // 1 KB transfers of hidden rows per stage
+  static constexpr int PH = (XH + kWaves - 1) / kWaves, FULLH = XH - (PH - 1) * kWaves;  // waves that issue PH, else PH - 1
+  static constexpr int PW = NT / 8 / kWaves;          // transfers of weight rows per wave
+  static_assert(NS >= 3, "ring depth");
+};
+
+template <int RB, int WR, bool BF16OUT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void lmh_low(LmhParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  using G = LowGeo<RB, WR>;
+  constexpr int CB = G::CB, WC = G::WC, NS = G::NS;
+  __shared__ __attribute__((aligned(1024))) char lds[NS * G::STAGE + G::RED];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = w / WC, wc = w % WC;
+  const int l16 = lane & 15, grp = lane >> 4;
+
+  // Transfer j of a matrix fills 1 KB: its LDS rows 8 j .. 8 j + 7, lane l
+  // chunk l % 8 of row 8 j + l / 8; wave w issues transfers w, w + 8, ...
+  const uint32_t lrow = (uint32_t)(8 * w + lane / 8), lchunk = (uint32_t)((lane % 8) ^ lmh_swz(lane / 8)) * 16u;
+  uint32_t hoff[G::PH], woff[G::PW];
+#pragma unroll
+  for (int q = 0; q < G::PH; ++q) hoff[q] = (lrow + 64u * q) * (uint32_t)(p.h_st * 2) + lchunk;
+#pragma unroll
+  for (int q = 0; q < G::PW; ++q) woff[q] = (lrow + 64u * q) * (uint32_t)(p.w_st * 2) + lchunk;
+  const bool fullh = w < G::FULLH;                    // wave-uniform
+  const int nk = (p.K + 63) / 64;
+  const __amdgpu_buffer_rsrc_t rh = lmh_rows(p.hidden, p.M, p.h_st, p.K);
+
+  // The ring runs on over this work-group's tiles (blockIdx.x, + gridDim.x,
+  // ...): the next tile's first slices are in flight during a tile's last
+  // ones and its epilogue.  Past the last tile the weights' descriptor is
+  // empty (zeros, no traffic).
+  int ilt = blockIdx.x, it = 0, iks = lmh_first_slice(p, ilt, nk);   // tile, slice count and k slice to issue
+  auto wrows = [&](int nt) {
+    return lmh_rows(p.weight + (int64_t)nt * G::NT * p.w_st, min(G::NT, p.V - nt * G::NT), p.w_st, p.K);
+  };
+  __amdgpu_buffer_rsrc_t rw = wrows(ilt);
+  auto issue = [&](int stage) {
+    char* base = lds + stage * G::STAGE + w * 1024;
+    const uint32_t koff = (uint32_t)iks * kRowB;
+#pragma unroll
+    for (int q = 0; q < G::PW; ++q)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void_t*)(base + G::RA * kRowB + q * 8192), 16, woff[q] + koff, 0,
+                                               0, SV_LMH_W_CPOL);
+#pragma unroll
+    for (int q = 0; q < G::PH; ++q)
+      if (q < G::PH - 1 || fullh)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rh, (lds_void_t*)(base + q * 8192), 16, hoff[q] + koff, 0, 0, 0);
+    if (++iks == nk) iks = 0;
+    if (++it == nk) {
+      it = 0;
+      ilt += gridDim.x;
+      iks = lmh_first_slice(p, ilt, nk);
+      rw = wrows(ilt);
+    }
+  };
+  uint32_t ch[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) ch[h] = (uint32_t)(((4 * h + grp) ^ lmh_swz(l16)) * 16);
+  const uint32_t abase = (uint32_t)(16 * RB * wr + l16) * kRowB;
+  const uint32_t bbase = (uint32_t)(G::RA + 16 * CB * wc + l16) * kRowB;
+#pragma unroll
+  for (int st = 0; st < NS - 1; ++st) issue(st);
+  lmh_setup(p);                     // its host reads fly beside the first slices
+  int stage = 0;
+  for (int nt = blockIdx.x; nt < p.ntiles; nt += gridDim.x) {
+    f32x4 acc[RB][CB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < nk; ++t) {
+      // this wave's transfers of the current slice have landed (the NS - 2
+      // after it may still fly)
+      if (fullh) lmh_wait_vm<(G::PH + G::PW) * (NS - 2)>();
+      else lmh_wait_vm<(G::PH - 1 + G::PW) * (NS - 2)>();
+      lmh_barrier();                // everyone's have; the stage read last is free
+      issue(stage == 0 ? NS - 1 : stage - 1);
+      const char* sb = lds + stage * G::STAGE;
+      stage = stage + 1 == NS ? 0 : stage + 1;
+      bf16x8 a[2][RB], b[2][CB];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) b[h][cb] = *reinterpret_cast<const bf16x8*>(sb + bbase + cb * 16 * kRowB + ch[h]);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) a[h][rb] = *reinterpret_cast<const bf16x8*>(sb + abase + rb * 16 * kRowB + ch[h]);
+      }
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][rb], b[0][cb], acc[rb][cb], 0, 0, 0);
+      // K % 64 == 32: the last k slice (no rotation then) holds 32 k only
+      if (t + 1 < nk || p.K % 64 == 0) {              // wave-uniform
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb)
+            acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][rb], b[1][cb], acc[rb][cb], 0, 0, 0);
+      }
+    }
+    const LmhTile tile{0, p.M, nt, nt * G::NT, min(G::NT, p.V - nt * G::NT)};
+    lmh_epilogue<RB, CB, WR, WC, BF16OUT>(p, tile, acc, lds + NS * G::STAGE, wr, wc, lane);
   }
 #endif
 }
 
+// ---------------------------------------------------------------------------
+// Tall tiles: up to 64 RB rows x 256 vocabulary entries, bound by the matrix
+// cores.
+// ---------------------------------------------------------------------------
 template <int RB>
-hipError_t launch_rb(const LmhParams& p, hipStream_t s) {
-  const int groups = (p.ntiles + 7) / 8;
-  const dim3 grid((unsigned)(groups * 8 * p.m_tiles));
-  if (p.out_bf16) lmh_gemm<RB, true><<<grid, dim3(kLmhThreads), 0, s>>>(p);
-  else lmh_gemm<RB, false><<<grid, dim3(kLmhThreads), 0, s>>>(p);
+struct TallGeo {
+  static constexpr int WR = 4, WC = 2, NT = kLmhNT, CB = NT / (16 * WC);
+  static constexpr int RA = 16 * RB * WR;
+  static constexpr int HST = RA * kRowB, WST = NT * kRowB;            // bytes of a slice of each matrix
+  static constexpr int XH = RA / 8 / kWaves, XW = NT / 8 / kWaves;    // transfers per wave and slice
+  // slices in LDS: two of the hidden rows (L2 hits), and as many of the
+  // weights (from HBM) as fit, at most three
+  static constexpr int NW = 2 * HST + 3 * WST <= kLdsBytes ? 3 : 2;
+  static constexpr int LDS = 2 * HST + NW * WST;
+  // A slice's transfers are issued after the barrier that frees their stages,
+  // or spread over the column blocks behind it.  Together they start sooner
+  // but hold the waves' next products back: 192- and 384-row tiles measured
+  // 109.6 and 181 us together, 112.7 and 187 spread (320 and 700 rows x 4096 x
+  // 32000 with the acceptance), 256-row tiles 134.9 and 131.2 (480 rows).
+  static constexpr bool SPREAD = RB == 4;
+  static_assert(RA % 64 == 0 && LDS <= kLdsBytes, "two slices in LDS");
+};
+
+template <int RB, bool BF16OUT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void lmh_tall(LmhParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  using G = TallGeo<RB>;
+  constexpr int CB = G::CB, WR = G::WR, WC = G::WC;
+  __shared__ __attribute__((aligned(1024))) char lds[G::LDS];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = w / WC, wc = w % WC;
+  const int l16 = lane & 15, grp = lane >> 4;
+  const LmhTile it = lmh_tile<G::NT>(p, blockIdx.x);
+  if (it.ncols <= 0 || it.mrows <= 0) {               // uniform
+    lmh_setup(p);
+    return;
+  }
+  const uint32_t lrow = (uint32_t)(8 * w + lane / 8), lchunk = (uint32_t)((lane % 8) ^ lmh_swz(lane / 8)) * 16u;
+  const uint32_t hoff = lrow * (uint32_t)(p.h_st * 2) + lchunk, woff = lrow * (uint32_t)(p.w_st * 2) + lchunk;
+  const int nk = (p.K + 63) / 64;
+  const int k0 = lmh_first_slice(p, it.nt, nk);
+  // Transfer q of slice t of a matrix into stage st.  Past the last slice the
+  // descriptor is empty (zeros, no traffic), so that the transfer counts stay
+  // the same.  The step between transfers is opaque: their offsets are formed
+  // here and do not each hold a register through the loop.
+  auto kbytes = [&](int t) { return (uint32_t)(t + k0 < nk ? t + k0 : t + k0 - nk) * kRowB; };
+  auto xfer_h = [&](int st, int t, int q) {
+    const __amdgpu_buffer_rsrc_t r = lmh_rows(p.hidden + it.m0 * p.h_st, t < nk ? it.mrows : 0, p.h_st, p.K);
+    uint32_t step = 128u * (uint32_t)p.h_st;          // 64 rows
+    asm volatile("" : "+s"(step));
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(lds + st * G::HST + w * 1024 + q * 8192), 16,
+                                             hoff + (q * step + kbytes(t)), 0, 0, 0);
+  };
+  auto xfer_w = [&](int st, int t, int q) {
+    const __amdgpu_buffer_rsrc_t r = lmh_rows(p.weight + it.n0 * p.w_st, t < nk ? it.ncols : 0, p.w_st, p.K);
+    uint32_t step = 128u * (uint32_t)p.w_st;
+    asm volatile("" : "+s"(step));
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        r, (lds_void_t*)(lds + 2 * G::HST + st * G::WST + w * 1024 + q * 8192), 16, woff + (q * step + kbytes(t)), 0, 0,
+        0);
+  };
+  // LDS addresses of this lane's operands, by k half, in the stage being read
+  // (updated as the walk changes stage)
+  uint32_t aad[2], bad[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t c = (uint32_t)(((4 * h + grp) ^ lmh_swz(l16)) * 16);
+    aad[h] = (uint32_t)(16 * RB * wr + l16) * kRowB + c;
+    bad[h] = (uint32_t)(2 * G::HST) + (uint32_t)(16 * CB * wc + l16) * kRowB + c;
+  }
+
+  f32x4 acc[RB][CB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 a[RB], b[2];
+  auto lda = [&](int h, int rb) { return *reinterpret_cast<const bf16x8*>(lds + aad[h] + rb * 16 * kRowB); };
+  auto ldb = [&](int h, int cb) { return *reinterpret_cast<const bf16x8*>(lds + bad[h] + cb * 16 * kRowB); };
+#pragma unroll
+  for (int q = 0; q < G::XW; ++q) xfer_w(0, 0, q);
+#pragma unroll
+  for (int q = 0; q < G::XH; ++q) xfer_h(0, 0, q);
+  if constexpr (G::NW == 3)
+#pragma unroll
+    for (int q = 0; q < G::XW; ++q) xfer_w(1, 1, q);
+  lmh_setup(p);                     // its host reads fly beside the first slices
+  lmh_wait_vm<(G::NW - 2) * G::XW>();
+  lmh_barrier();
+  b[0] = ldb(0, 0);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) a[rb] = lda(0, rb);
+  // Half H (32 k) of a slice: the hidden rows' operands stay in registers, the
+  // weight operands pass through two, each loaded one column block ahead; in
+  // the last column block each hidden operand is replaced by the next half's
+  // as its last product is issued (past the last slice: by what the ring
+  // holds, never used).
+  int hstep = G::HST, wstage = 0;   // to the other stage of the hidden rows; the weights' stage
+  // During slice s (or, together, from the barrier that ends slice s - 1):
+  // transfers h0 .. h1 of the hidden rows' slice s + 1 and w0 .. w1 of the
+  // weights' slice s + NW - 1, into the stages that slice s - 1 left.
+  auto ahead = [&](int s, int h0, int h1, int w0, int w1) {
+    const int hs = (s + 1) & 1, ws = wstage == 0 ? G::NW - 1 : wstage - 1;
+#pragma unroll
+    for (int q = h0; q < h1; ++q) xfer_h(hs, s + 1, q);
+#pragma unroll
+    for (int q = w0; q < w1; ++q) xfer_w(ws, s + G::NW - 1, q);
+  };
+  if constexpr (!G::SPREAD) ahead(0, 0, G::XH, 0, G::XW);
+  auto half = [&](auto hc, int t) {
+    constexpr int H = decltype(hc)::value;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      if (H == 1 && cb + 1 == CB) {
+        // Every operand of this slice has been read: the next slice has landed
+        // (the weights of the one after may still fly), everyone is done
+        // with this one, and later slices may overwrite it.
+        lmh_wait_vm<(G::NW - 2) * G::XW>();
+        lmh_barrier();
+        const int wstep = wstage + 1 == G::NW ? -(G::NW - 1) * G::WST : G::WST;
+        wstage = wstage + 1 == G::NW ? 0 : wstage + 1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          aad[h] += hstep;
+          bad[h] += wstep;
+        }
+        hstep = -hstep;
+        if constexpr (!G::SPREAD) ahead(t + 1, 0, G::XH, 0, G::XW);
+      } else if constexpr (G::SPREAD) {
+        if (H == 0 && cb < G::XH) ahead(t, cb, cb + 1, 0, 0);
+        if (H == 1 && cb < G::XW) ahead(t, 0, 0, cb, cb + 1);
+      }
+      b[(cb + 1) & 1] = cb + 1 < CB ? ldb(H, cb + 1) : ldb(1 - H, 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb], b[cb & 1], acc[rb][cb], 0, 0, 0);
+        if (cb + 1 == CB) {
+          a[rb] = lda(1 - H, rb);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  static_assert(CB % 2 == 0, "the weight operands alternate over two registers");
+  for (int t = 0; t < p.K / 64; ++t) {
+    half(std::integral_constant<int, 0>{}, t);
+    half(std::integral_constant<int, 1>{}, t);
+  }
+  if (p.K % 64 != 0) half(std::integral_constant<int, 0>{}, nk - 1);   // the last slice holds 32 k only
+  lmh_wait_vm<0>();
+  lmh_barrier();                    // the ring is no longer read: reuse its LDS
+  int elane = threadIdx.x & 63;     // opaque: keeps the epilogue's addresses out of the loop's registers
+  asm volatile("" : "+v"(elane));
+  lmh_epilogue<RB, CB, WR, WC, BF16OUT>(p, it, acc, lds, wr, wc, elane);
+#endif
+}
+
+template <int RB, int WR>
+hipError_t launch_low(const LmhParams& p, int cus, hipStream_t s) {
+  const dim3 grid((unsigned)std::min(p.ntiles, std::max(cus, 1)));
+  if (p.out_bf16) lmh_low<RB, WR, true><<<grid, dim3(kThreads), 0, s>>>(p);
+  else lmh_low<RB, WR, false><<<grid, dim3(kThreads), 0, s>>>(p);
+  return hipGetLastError();
+}
+template <int RB>
+hipError_t launch_tall(const LmhParams& p, hipStream_t s) {
+  const dim3 grid((unsigned)(((p.ntiles + 7) / 8) * 8 * p.m_tiles));
+  if (p.out_bf16) lmh_tall<RB, true><<<grid, dim3(kThreads), 0, s>>>(p);
+  else lmh_tall<RB, false><<<grid, dim3(kThreads), 0, s>>>(p);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// Tile height for M rows and ntiles vocabulary tiles.  Every CU fetches
-// its operands from L2 at a fixed rate of cache lines, so a launch costs
-// about (rounds of work-groups over the CUs) x (lines per k slice: the
-// tile's hidden rows + 256 weight rows); the height with the lowest cost
-// wins (ties: the lower one, fewer idle MFMAs), and its row tiles are
-// balanced (rows past M read as zeros and cost no line).
-LmhGeometry lmh_geometry(int M, int ntiles, int cus) {
-  LmhGeometry best{};
-  int64_t best_cost = -1;
-  for (int rb = 1; rb <= SV_LMH_MAXRB; ++rb) {
-    const int ra = 16 * kWR * rb;
-    const int m_tiles = (M + ra - 1) / ra;
-    const int rows = (M + m_tiles - 1) / m_tiles;
-    const int64_t groups = (int64_t)m_tiles * ntiles;
-    const int64_t cost = ((groups + cus - 1) / cus) * (int64_t)(rows + kLmhNT);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best = LmhGeometry{rb, rows, m_tiles};
+// Tile shape for M rows and V vocabulary entries, in units of about 14 us at
+// K = 4096:
+//  - low tiles take every row at once (M <= 192); they leave the chip half
+//    empty where the vocabulary has few tiles (M = 160, V = 9000: 70 us
+//    against 56 for 64-row tall tiles);
+//  - tall tiles cost about RB + 3 a round of work-groups over the CUs (the
+//    products, and the prologue, epilogue and slice hand-overs), M = 240 to
+//    960 at V = 32000 within a few percent; rows past M read as zeros and cost
+//    no traffic, so the row tiles are balanced.
+// At M = 110 / 160 / 192, V = 32000: low 68 / 75 / 83 us, tall 78 / 90 / 91.
+LmhGeometry lmh_geometry(int M, int V, int cus) {
+  LmhGeometry g{};
+  const int64_t low_tiles = ((int64_t)V + kLmhNTLow - 1) / kLmhNTLow;
+  if (M <= 64 || (M <= 192 && 2 * low_tiles > cus)) {
+    g.low_wr = M <= 96 ? 1 : 2;
+    g.rb = (M + 16 * g.low_wr - 1) / (16 * g.low_wr);
+    g.m_tiles = 1;
+    g.nt = kLmhNTLow;
+  } else {
+    int64_t best = -1;
+    for (int rb = 1; rb <= 6; ++rb) {
+      const int64_t mt = (M + 64 * rb - 1) / (64 * rb);
+      const int64_t groups = mt * (((int64_t)V + kLmhNT - 1) / kLmhNT);
+      const int64_t cost = (groups + cus - 1) / cus * (rb + 3);
+      if (best < 0 || cost < best) {
+        best = cost;
+        g.rb = rb;
+        g.m_tiles = (int32_t)mt;
+      }
     }
+    g.nt = kLmhNT;
   }
-  return best;
+  g.tile_rows = (M + g.m_tiles - 1) / g.m_tiles;
+  return g;
 }
 
-hipError_t launch_lmh(const LmhParams& p, hipStream_t s) {
-  if (p.M < 1 || p.tile_rows < 1 || p.tile_rows > 16 * kWR * p.rb || p.m_tiles != (p.M + p.tile_rows - 1) / p.tile_rows)
-    return hipErrorInvalidValue;
+hipError_t launch_lmh(const LmhParams& p, int cus, hipStream_t s) {
+  if (p.M < 1 || p.tile_rows < 1 || p.m_tiles != (p.M + p.tile_rows - 1) / p.tile_rows) return hipErrorInvalidValue;
+  if (p.low_wr) {
+    if (p.m_tiles != 1 || p.M > 16 * p.rb * p.low_wr) return hipErrorInvalidValue;
+    switch (p.low_wr * 16 + p.rb) {
+      case 16 + 1: return launch_low<1, 1>(p, cus, s);
+      case 16 + 2: return launch_low<2, 1>(p, cus, s);
+      case 16 + 3: return launch_low<3, 1>(p, cus, s);
+      case 16 + 4: return launch_low<4, 1>(p, cus, s);
+      case 16 + 5: return launch_low<5, 1>(p, cus, s);
+      case 16 + 6: return launch_low<6, 1>(p, cus, s);
+      case 32 + 4: return launch_low<4, 2>(p, cus, s);
+      case 32 + 5: return launch_low<5, 2>(p, cus, s);
+      case 32 + 6: return launch_low<6, 2>(p, cus, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (p.tile_rows > 64 * p.rb) return hipErrorInvalidValue;
   switch (p.rb) {
-    case 1: return launch_rb<1>(p, s);
-    case 2: return launch_rb<2>(p, s);
-#if SV_LMH_MAXRB >= 3
-    case 3: return launch_rb<3>(p, s);
-#endif
-#if SV_LMH_MAXRB >= 4
-    case 4: return launch_rb<4>(p, s);
-#endif
-#if SV_LMH_MAXRB >= 8
-    case 5: return launch_rb<5>(p, s);
-    case 6: return launch_rb<6>(p, s);
-    case 7: return launch_rb<7>(p, s);
-    case 8: return launch_rb<8>(p, s);
-#endif
+    case 1: return launch_tall<1>(p, s);
+    case 2: return launch_tall<2>(p, s);
+    case 3: return launch_tall<3>(p, s);
+    case 4: return launch_tall<4>(p, s);
+    case 5: return launch_tall<5>(p, s);
+    case 6: return launch_tall<6>(p, s);
     default: return hipErrorInvalidValue;
   }
 }

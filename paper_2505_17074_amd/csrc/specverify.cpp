@@ -676,20 +676,20 @@ spec_status_t check_lm(const spec_lm_head_args_t* lm) {
     return SPEC_ERR_INVALID_ARG;
   // each work-group's rows are addressed with 32-bit offsets
   if ((int64_t)sv::kLmhNT * lm->weight_stride * 2 >= INT32_MAX ||
-      (int64_t)sv::kLmhMaxTileRows * lm->hidden_stride * 2 >= INT32_MAX)
+      (int64_t)sv::kLmhOffsetRows * lm->hidden_stride * 2 >= INT32_MAX)
     return SPEC_ERR_UNSUPPORTED;
   return SPEC_OK;
 }
 
 // The LM-head call's plan: the acceptance plan plus the tile statistics
-// [Nq, ceil(V / 256)] at the end of the workspace.
+// (at most [Nq, ceil(V / 128)]) at the end of the workspace.
 spec_status_t lm_plan(const spec_requests_t* req, const spec_lm_head_args_t* lm, const spec_accept_args_t* acc,
                       Plan& P, size_t& off_tiles, size_t& device_bytes) {
   if (!acc) return SPEC_ERR_INVALID_ARG;
   spec_status_t st = build_plan(req, nullptr, acc, P);
   if (st != SPEC_OK) return st;
   if ((st = check_lm(lm)) != SPEC_OK) return st;
-  const int64_t ntiles = (acc->vocab + sv::kLmhNT - 1) / sv::kLmhNT;
+  const int64_t ntiles = ((int64_t)acc->vocab + sv::kLmhNTLow - 1) / sv::kLmhNTLow;   // whichever tiles run
   off_tiles = P.device_bytes;
   device_bytes = align_up(off_tiles + sizeof(sv::ChunkStat) * (size_t)(P.Nq * ntiles));
   return SPEC_OK;
@@ -846,9 +846,10 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
     g.M = (int32_t)P.Nq;
     g.K = lm->hidden_dim;
     g.V = acc->vocab;
-    g.ntiles = (acc->vocab + sv::kLmhNT - 1) / sv::kLmhNT;
-    const sv::LmhGeometry geo = sv::lmh_geometry(g.M, g.ntiles, device_cus());
+    const sv::LmhGeometry geo = sv::lmh_geometry(g.M, g.V, device_cus());
+    g.ntiles = (acc->vocab + geo.nt - 1) / geo.nt;
     g.rb = geo.rb;
+    g.low_wr = geo.low_wr;
     g.tile_rows = geo.tile_rows;
     g.m_tiles = geo.m_tiles;
     g.out_bf16 = acc->dtype == SPEC_BF16;
@@ -859,6 +860,7 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
     if (!fold) {
       c.tiles = g.tiles;
       c.ntiles = g.ntiles;
+      c.tpc = sv::kAccChunk / geo.nt;
       g.reqs_src = c.reqs_src;
       g.reqs = c.reqs;
       g.tickets = c.tickets;
@@ -868,10 +870,10 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
       g.B = c.B;
     }
     if (lm->event_begin && hipEventRecord(static_cast<hipEvent_t>(lm->event_begin), s) != hipSuccess) return SPEC_ERR_HIP;
-    if (sv::launch_lmh(g, s) != hipSuccess) return SPEC_ERR_HIP;
+    if (sv::launch_lmh(g, device_cus(), s) != hipSuccess) return SPEC_ERR_HIP;
     if (lm->event_end && hipEventRecord(static_cast<hipEvent_t>(lm->event_end), s) != hipSuccess) return SPEC_ERR_HIP;
     if (acc->event_begin && hipEventRecord(static_cast<hipEvent_t>(acc->event_begin), s) != hipSuccess) return SPEC_ERR_HIP;
-    if (fold && sv::launch_foldstats(c, g.tiles, g.ntiles, s) != hipSuccess) return SPEC_ERR_HIP;
+    if (fold && sv::launch_foldstats(c, g.tiles, g.ntiles, sv::kAccChunk / geo.nt, s) != hipSuccess) return SPEC_ERR_HIP;
     if (acc->event_mid && hipEventRecord(static_cast<hipEvent_t>(acc->event_mid), s) != hipSuccess) return SPEC_ERR_HIP;
     if (sv::launch_decide(c, s) != hipSuccess) return SPEC_ERR_HIP;
     if (acc->event_end && hipEventRecord(static_cast<hipEvent_t>(acc->event_end), s) != hipSuccess) return SPEC_ERR_HIP;

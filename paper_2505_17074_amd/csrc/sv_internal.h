@@ -80,18 +80,19 @@ struct AccParams {
   int32_t seq_groups;
   SeqSlot* seq_slots;
   // after the LM head (tiles != nullptr): the decision kernel folds the GEMM's
-  // per-(row, kLmhNT-entry tile) statistics itself [Nq, ntiles], and rowstats
-  // is not written
+  // per-(row, vocabulary tile) statistics itself [Nq, ntiles], and rowstats is
+  // not written; tpc tiles per chunk
   const ChunkStat* tiles;
   int32_t ntiles;
+  int32_t tpc;
 };
 
 constexpr int kAccMaxChunks = 1024;    // vocabularies up to 4M entries
 
 // The target model's LM head, logits = hidden . weight^T, with the softmax
-// statistics of each (row, kLmhNT-entry tile) taken in the epilogue.
-constexpr int kLmhNT = 256;            // vocabulary entries per work-group and statistics tile
-constexpr int kLmhTilesPerChunk = kAccChunk / kLmhNT;
+// statistics of each (row, vocabulary tile) taken in the epilogue.
+constexpr int kLmhNT = 256;            // vocabulary entries per work-group and statistics tile: tall tiles
+constexpr int kLmhNTLow = 128;         // and low ones
 struct LmhParams {
   const uint16_t* hidden;   // [M, K] bf16, row stride h_st elements
   const uint16_t* weight;   // [V, K] bf16, row stride w_st elements
@@ -101,8 +102,9 @@ struct LmhParams {
   ChunkStat* tiles;         // [M, ntiles] per-tile (sum of exp(l - max), max)
   int32_t M, K, V, ntiles;
   int32_t m_tiles;          // row tiles of tile_rows rows (the last one may be shorter)
-  int32_t tile_rows;        // <= the kernel's tile height 64 rb
-  int32_t rb;               // 16-row blocks per wave: tile height 64 rb
+  int32_t tile_rows;        // <= the kernel's tile height
+  int32_t rb;               // 16-row blocks per wave: tile height 16 rb low_wr (low tiles) or 64 rb (tall)
+  int32_t low_wr;           // low tiles: waves along the rows (1 or 2); 0: tall tiles
   int32_t out_bf16;
   // the row-statistics kernel's other duties for the decision kernel that
   // follows: the request table's device copy (and the node table's, per-request
@@ -116,17 +118,17 @@ struct LmhParams {
   int32_t B;
 };
 struct LmhGeometry {
-  int32_t rb, tile_rows, m_tiles;
+  int32_t rb, low_wr, tile_rows, m_tiles, nt;   // nt: vocabulary entries per tile
 };
-constexpr int kLmhMaxTileRows = 256;   // 16 x waves along the rows x row blocks per wave, at most
-// The tile height and row tiles for M rows, ntiles vocabulary tiles and cus
+constexpr int kLmhOffsetRows = 256;    // rows of hidden whose offsets the host keeps below 2^31
+// The tile shape and row tiles for M rows, V vocabulary entries and cus
 // compute units.
-LmhGeometry lmh_geometry(int M, int ntiles, int cus);
-hipError_t launch_lmh(const LmhParams& p, hipStream_t s);
+LmhGeometry lmh_geometry(int M, int V, int cus);
+hipError_t launch_lmh(const LmhParams& p, int cus, hipStream_t s);
 // Chunk statistics [Nq, nch] (the decision kernel's input) folded from the
 // LM head's tile statistics, plus the row-statistics kernel's other duties
 // (the request and node tables' device copies, cleared tickets).
-hipError_t launch_foldstats(const AccParams& p, const ChunkStat* tiles, int ntiles, hipStream_t s);
+hipError_t launch_foldstats(const AccParams& p, const ChunkStat* tiles, int ntiles, int tpc, hipStream_t s);
 
 // exp(x - m) for x <= m (a logit against a maximum): the hardware base-2
 // exponential of (x - m) log2 e.  Its error is about an ulp of the result
