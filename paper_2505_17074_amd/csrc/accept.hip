@@ -66,16 +66,76 @@ __device__ __forceinline__ float ld(const uint16_t* p, int64_t i) {
   return __uint_as_float(static_cast<uint32_t>(p[i]) << 16);
 }
 
+// Reductions over a wave's 64 lanes, every lane getting the result: DPP steps
+// inside the 16-lane rows (pairs, quads, then mirrored quads and halves, which
+// hold uniform values by then) and two LDS shuffles across the rows.  Six
+// shuffles took about 60 cycles of latency each, the DPP steps under ten.
+__device__ __forceinline__ float wave_max(float x) {
+  x = max16(x);
+  x = fmaxf(x, __shfl_xor(x, 16));
+  return fmaxf(x, __shfl_xor(x, 32));
+}
+__device__ __forceinline__ double wave_sum(double x) {
+  x = sum16(x);
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
+}
+
+__device__ __forceinline__ int wave_max(int x) {
+  x = max16(x);
+  x = max(x, __shfl_xor(x, 16));
+  return max(x, __shfl_xor(x, 32));
+}
+
+// The chunk that holds target among n chunk masses (LDS), by one wave: the
+// smallest whose cumulative mass exceeds it, *cum its prefix; a target rounded
+// past the total takes the last chunk with mass (0 where none has any).  64
+// masses a pass, their prefixes from one scan (one thread walking 32 masses
+// took 2 us).
+__device__ __forceinline__ int pick_chunk(const double* mass, int n, double target, double* cum) {
+  const int ln = threadIdx.x & 63;
+  double carry = 0.0, last_cum = 0.0;
+  int last = 0;
+  for (int b = 0; b < n; b += 64) {
+    const double v = b + ln < n ? mass[b + ln] : 0.0;
+    const double incl = carry + wave_scan(v);
+    double ex = __shfl_up(incl, 1);
+    if (ln == 0) ex = carry;
+    const unsigned long long over = __ballot(v > 0.0 && incl > target);
+    if (over) {
+      const int l = __builtin_ctzll(over);
+      *cum = __shfl(ex, l);
+      return b + l;
+    }
+    const unsigned long long pos = __ballot(v > 0.0);
+    if (pos) {
+      const int l = 63 - __builtin_clzll(pos);
+      last = b + l;
+      last_cum = __shfl(ex, l);
+    }
+    carry = __shfl(incl, 63);
+  }
+  *cum = last_cum;
+  return last;
+}
+// The sum of n masses (LDS), as pick_chunk's scan takes it.
+__device__ __forceinline__ double total_mass(const double* mass, int n) {
+  const int ln = threadIdx.x & 63;
+  double carry = 0.0;
+  for (int b = 0; b < n; b += 64) carry = __shfl(carry + wave_scan(b + ln < n ? mass[b + ln] : 0.0), 63);
+  return carry;
+}
+
 // Block-wide reductions over 256 threads (4 waves); `red` holds 4 values.
 __device__ __forceinline__ float block_max(float x, float* red) {
-  for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
+  x = wave_max(x);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
   return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 __device__ __forceinline__ double block_sum(double x, double* red) {
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+  x = wave_sum(x);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
@@ -237,7 +297,7 @@ __global__ __launch_bounds__(kAccThreads) void acc_rowstats(AccParams p) {
     m[sc] = -INFINITY;
 #pragma unroll
     for (int k = 0; k < LPS * VW; ++k) m[sc] = fmaxf(m[sc], x[sc][k]);
-    for (int o = 32; o >= 1; o >>= 1) m[sc] = fmaxf(m[sc], __shfl_xor(m[sc], o));
+    m[sc] = wave_max(m[sc]);
   }
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
@@ -251,7 +311,7 @@ __global__ __launch_bounds__(kAccThreads) void acc_rowstats(AccParams p) {
     sm[sc] = 0.0;
 #pragma unroll
     for (int k = 0; k < LPS * VW; ++k) sm[sc] += (double)exp_rel(x[sc][k], m[sc]);
-    for (int o = 32; o >= 1; o >>= 1) sm[sc] += __shfl_xor(sm[sc], o);
+    sm[sc] = wave_sum(sm[sc]);
   }
   if ((threadIdx.x & 63) == 0)
 #pragma unroll
@@ -366,7 +426,7 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
   __shared__ float s_mrow, s_mcc;
   __shared__ int s_chunk;
   __shared__ int s_cand[4], s_last_pos[4];
-  __shared__ int s_par[kMaxNodes], s_dep[kMaxNodes], s_qr[kMaxNodes];
+  __shared__ int s_dep[kMaxNodes], s_qr[kMaxNodes];
   const int i = blockIdx.x / p.nch, c = blockIdx.x % p.nch;
   const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63;
   SV_TRACE(1, 0);
@@ -380,11 +440,13 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
   // probability at it, and its uniform.
   const int n = tid;
   const bool tester = n >= 1 && n < N;      // lanes of wave 0 only (N <= 32)
-  int par = 0;
+  int par = 0, dep = 0;
+  uint32_t anc = 0u;                        // this node's path (a bit per node)
   float lx = 0.f, qx = 0.f, un = 0.f;
   if (n < N) {
     const NodeRec nr = node_rec(p, p.nodes, rq, n);
-    s_par[n] = nr.par;
+    anc = p.per_req ? p.nodes[rq.node0 + n].anc : p.topo.anc[n];
+    dep = nr.dep;
     s_dep[n] = nr.dep;
     s_qr[n] = nr.qr;
     if (tester) {
@@ -398,15 +460,45 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
   }
 
   // (M, Z) of every row of the request that has chunk statistics (after the
-  // LM head, its tile statistics: the same fold over 16 times as many entries)
-  // A row of at most 64 * kHeld tile statistics is loaded whole into
-  // registers before any is used (one round trip); chunk statistics (at
-  // most a few per lane) and longer rows take two passes.
+  // LM head, its tile statistics: the same fold over 16 or 32 times as many
+  // entries).  Chunk statistics fold on 16 lanes per row, so 16 rows take one
+  // round trip: a wave per row took one for every fourth row.  The tile
+  // statistics of a row take a wave; up to 64 * kHeld of them are loaded whole
+  // into registers before any is used (one round trip), more take two passes.
   constexpr int kHeld = TILES ? HELD : 1;
   const int nst = TILES ? p.ntiles : p.nch;
-  for (int r = wv; r < N; r += kAccThreads / 64) {
-    if (p.tree == 1 && !p.all_stats && p.topo.qrank[r] < 0) continue;     // a leaf's row: none yet
-    const ChunkStat* st = (TILES ? p.tiles : p.rowstats) + (int64_t)(rq.q0 + r) * nst;
+  if constexpr (!TILES) {
+    for (int r = tid >> 4; r < N; r += kAccThreads / 16) {
+      if (p.tree == 1 && !p.all_stats && p.topo.qrank[r] < 0) continue;   // a leaf's row: none yet
+      const ChunkStat* st = p.rowstats + (int64_t)(rq.q0 + r) * nst;
+      const int l = tid & 15;
+      // two statistics a lane (32 chunks, 131072 entries) in flight at once
+      float m0 = -INFINITY, m1 = -INFINITY;
+      double s0 = 0.0, s1 = 0.0;
+      if (l < nst) {
+        m0 = st[l].m;
+        s0 = st[l].s;
+      }
+      if (l + 16 < nst) {
+        m1 = st[l + 16].m;
+        s1 = st[l + 16].s;
+      }
+      float m = fmaxf(m0, m1);
+      for (int k = l + 32; k < nst; k += 16) m = fmaxf(m, st[k].m);
+      m = max16(m);
+      double z = 0.0;
+      if (l < nst) z += s0 * exp((double)m0 - (double)m);
+      if (l + 16 < nst) z += s1 * exp((double)m1 - (double)m);
+      for (int k = l + 32; k < nst; k += 16) z += st[k].s * exp((double)st[k].m - (double)m);
+      z = sum16(z);
+      if (l == 0) {
+        s_M[r] = m;
+        s_Z[r] = z;
+      }
+    }
+  }
+  for (int r = TILES ? wv : N; r < N; r += kAccThreads / 64) {
+    const ChunkStat* st = p.tiles + (int64_t)(rq.q0 + r) * nst;
     float m = -INFINITY;
     double z = 0.0;
     if (TILES && nst <= 64 * kHeld) {
@@ -423,16 +515,16 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
       }
 #pragma unroll
       for (int j = 0; j < kHeld; ++j) m = fmaxf(m, hm[j]);
-      for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+      m = wave_max(m);
 #pragma unroll
       for (int j = 0; j < kHeld; ++j)
         if (ln + 64 * j < nst) z += hs[j] * exp((double)hm[j] - (double)m);
     } else {
       for (int k = ln; k < nst; k += 64) m = fmaxf(m, st[k].m);
-      for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+      m = wave_max(m);
       for (int k = ln; k < nst; k += 64) z += st[k].s * exp((double)st[k].m - (double)m);
     }
-    for (int o = 32; o >= 1; o >>= 1) z += __shfl_xor(z, o);
+    z = wave_sum(z);
     if (ln == 0) {
       s_M[r] = m;
       s_Z[r] = z;
@@ -448,17 +540,14 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
       const double px = exp((double)lx - (double)s_M[par]) / s_Z[par];
       pass = (double)un * (double)qx < px;
     }
-    const unsigned long long passmask = __ballot(pass);
+    const uint32_t passmask = (uint32_t)__ballot(pass);     // nodes are lanes 0 .. 31
+    // node n is accepted iff every node of its path below the root passes; the
+    // deepest accepted node wins, the smallest index on ties
+    const bool acc = n < N && (anc & ~1u & ~passmask) == 0u;
+    int key = acc ? (dep << 8) | (255 - n) : 0;
+    for (int o = 16; o >= 1; o >>= 1) key = max(key, __shfl_xor(key, o));
     if (n == 0) {
-      uint32_t accepted = 1u;   // bit per node
-      int best = 0;
-      for (int m = 1; m < N; ++m) {
-        const int par = s_par[m];
-        if (((accepted >> par) & 1u) && ((passmask >> m) & 1ull)) {
-          accepted |= 1u << m;
-          if (s_dep[m] > s_dep[best]) best = m;
-        }
-      }
+      const int best = 255 - (key & 255);
       const int qrank = s_qr[best];
       Decision d;
       d.node = best;
@@ -533,10 +622,9 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
     if (p.nch > 1)
       for (int k = tid; k < p.nch; k += kAccThreads) s_mass[k] = load_dev(p.masses + (int64_t)i * p.nch + k);
     __syncthreads();
-    if (tid == 0) {
-      double tot = 0.0;
-      for (int k = 0; k < p.nch; ++k) tot += s_mass[k];
-      s_tot = tot;
+    if (tid < 64) {
+      const double tot = total_mass(s_mass, p.nch);
+      if (tid == 0) s_tot = tot;
     }
     __syncthreads();
     // zero residual mass (reachable only through rounding): sample from p
@@ -589,49 +677,39 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
       }
     }
     __syncthreads();
-    if (tid == 0) {
+    if (tid < 64) {
       float mx = -INFINITY;
-      for (int k = 0; k < p.nch; ++k) mx = fmaxf(mx, s_mc[k]);
-      double tot = 0.0;
-      for (int k = 0; k < p.nch; ++k) {
-        s_mass[k] = s_mass[k] * exp((double)s_mc[k] - (double)mx);
-        tot += s_mass[k];
+      for (int k = tid; k < p.nch; k += 64) mx = fmaxf(mx, s_mc[k]);
+      mx = wave_max(mx);
+      // (one wave: its LDS accesses are in order)
+      for (int k = tid; k < p.nch; k += 64) s_mass[k] = s_mass[k] * exp((double)s_mc[k] - (double)mx);
+      const double tot = total_mass(s_mass, p.nch);
+      if (tid == 0) {
+        s_tot = tot;
+        s_mrow = mx;                // the row's max M
       }
-      s_tot = tot;
-      s_mrow = mx;                  // the row's max M
     }
     __syncthreads();
   }
   SV_TRACE(1, 5);
   const float u = p.uniforms[rq.q0 + N - 1];
-  if (tid == 0) {
-    const double tot = s_tot;
-    const double target = (double)u * tot;
-    double cum = 0.0;
-    int chosen = -1, last_pos = 0;
-    for (int k = 0; k < p.nch; ++k) {
-      if (s_mass[k] > 0.0) last_pos = k;
-      if (chosen < 0) {
-        if (cum + s_mass[k] > target) chosen = k;
-        else cum += s_mass[k];
+  if (tid < 64) {
+    const double target = (double)u * s_tot;
+    double cum;
+    const int chosen = pick_chunk(s_mass, p.nch, target, &cum);
+    if (tid == 0) {
+      s_chunk = chosen;
+      if (residual) {
+        s_mcc = 0.f;
+        s_base = cum;
+        s_target = target;
+      } else {
+        // the scan below runs in the chunk's own units exp(l - m_c)
+        const float mc = s_mc[chosen];
+        s_mcc = mc;
+        s_base = 0.0;
+        s_target = (target - cum) / exp((double)mc - (double)s_mrow);
       }
-    }
-    if (chosen < 0) {   // target rounded past the total: last chunk with mass
-      chosen = last_pos;
-      cum = 0.0;
-      for (int k = 0; k < chosen; ++k) cum += s_mass[k];
-    }
-    s_chunk = chosen;
-    if (residual) {
-      s_mcc = 0.f;
-      s_base = cum;
-      s_target = target;
-    } else {
-      // the scan below runs in the chunk's own units exp(l - m_c)
-      const float mc = s_mc[chosen];
-      s_mcc = mc;
-      s_base = 0.0;
-      s_target = (target - cum) / exp((double)mc - (double)s_mrow);
     }
   }
   __syncthreads();
@@ -654,12 +732,8 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
   if (tid < 64) {
     const double a0 = s_tsum[4 * tid], a1 = s_tsum[4 * tid + 1], a2 = s_tsum[4 * tid + 2];
     const double lsum = ((a0 + a1) + a2) + s_tsum[4 * tid + 3];
-    double incl = lsum;
-    for (int o = 1; o < 64; o <<= 1) {
-      const double y = __shfl_up(incl, o);
-      if (tid >= o) incl += y;
-    }
-    double ex = incl - lsum;
+    double ex = __shfl_up(wave_scan(lsum), 1);
+    if (tid == 0) ex = 0.0;
     s_tsum[4 * tid] = ex;
     ex += a0;
     s_tsum[4 * tid + 1] = ex;
@@ -682,10 +756,8 @@ __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
     }
   }
   // smallest crossing token, else the chunk's last positive weight
-  for (int o = 32; o >= 1; o >>= 1) {
-    cand = min(cand, __shfl_xor(cand, o));
-    lastpos = max(lastpos, __shfl_xor(lastpos, o));
-  }
+  cand = -wave_max(-cand);
+  lastpos = wave_max(lastpos);
   if ((tid & 63) == 0) {
     s_cand[tid >> 6] = cand;
     s_last_pos[tid >> 6] = lastpos;

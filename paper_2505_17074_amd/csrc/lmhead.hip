@@ -113,37 +113,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t lmh_rows(const uint16_t* src, 
   return __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, (uint32_t)bytes, 0x00020000);
 }
 
-// Reductions over the 16 lanes of a DPP row (all of them get the result): the
-// pairs, the quads, then quad against quad and half against half by
-// mirroring, which hold uniform values by then.  On the vector ALU: the LDS
-// shuffles they replace took most of the epilogue (see lmh_epilogue).
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-  const int v = __builtin_bit_cast(int, x);
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double x) {
-  const unsigned long long v = __builtin_bit_cast(unsigned long long, x);
-  const int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
-  const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, true);
-  const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, true);
-  return __builtin_bit_cast(double, ((unsigned long long)h << 32) | l);
-}
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
-__device__ __forceinline__ float max16(float x) {
-  x = fmaxf(x, dpp<kXor1>(x));
-  x = fmaxf(x, dpp<kXor2>(x));
-  x = fmaxf(x, dpp<kHalfMirror>(x));
-  return fmaxf(x, dpp<kMirror>(x));
-}
-__device__ __forceinline__ double sum16(double x) {
-  x += dpp<kXor1>(x);
-  x += dpp<kXor2>(x);
-  x += dpp<kHalfMirror>(x);
-  return x + dpp<kMirror>(x);
-}
-
 // Epilogue of one tile.  The logits are stored (fp32, or rounded to bf16),
 // and the statistics of each row over the tile's NT entries are taken on the
 // stored values: the maximum, then the sum of exp(l - max) in fp64, lane

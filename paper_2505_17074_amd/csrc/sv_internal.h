@@ -141,6 +141,63 @@ __device__ __forceinline__ float exp_rel(float x, float m) {
   return __builtin_amdgcn_exp2f((x - m) * 1.4426950408889634f);
 }
 
+// Reductions over the 16 lanes of a DPP row (all of them get the result): the
+// pairs, the quads, then quad against quad and half against half by
+// mirroring, which hold uniform values by then.  On the vector ALU, without an
+// LDS round trip per step.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  const int v = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const unsigned long long v = __builtin_bit_cast(unsigned long long, x);
+  const int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
+  const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, true);
+  const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)h << 32) | l);
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+__device__ __forceinline__ float max16(float x) {
+  x = fmaxf(x, dpp<kXor1>(x));
+  x = fmaxf(x, dpp<kXor2>(x));
+  x = fmaxf(x, dpp<kHalfMirror>(x));
+  return fmaxf(x, dpp<kMirror>(x));
+}
+__device__ __forceinline__ int max16(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, kXor1, 0xf, 0xf, true));
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, kXor2, 0xf, 0xf, true));
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, kHalfMirror, 0xf, 0xf, true));
+  return max(x, __builtin_amdgcn_update_dpp(x, x, kMirror, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double sum16(double x) {
+  x += dpp<kXor1>(x);
+  x += dpp<kXor2>(x);
+  x += dpp<kHalfMirror>(x);
+  return x + dpp<kMirror>(x);
+}
+
+// Inclusive sums over a wave's lanes in lane order: four shifted adds inside
+// each 16-lane row (zeros come in from outside), then the rows' totals.
+template <int CTRL>
+__device__ __forceinline__ double dpp_or_zero(double x) {
+  const unsigned long long v = __builtin_bit_cast(unsigned long long, x);
+  const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, false);
+  const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((unsigned long long)h << 32) | l);
+}
+__device__ __forceinline__ double wave_scan(double x) {
+  x += dpp_or_zero<0x111>(x);       // row_shr:1, 2, 4, 8
+  x += dpp_or_zero<0x112>(x);
+  x += dpp_or_zero<0x114>(x);
+  x += dpp_or_zero<0x118>(x);
+  const int row = (int)(threadIdx.x & 63) >> 4;
+  const double t0 = __shfl(x, 15), t1 = __shfl(x, 31), t2 = __shfl(x, 47);
+  if (row >= 1) x += row == 1 ? t0 : row == 2 ? t0 + t1 : (t0 + t1) + t2;
+  return x;
+}
+
 // Both acceptance kernels; `mid` (optional) is recorded between them.
 hipError_t launch_accept(const AccParams& p, hipStream_t s, hipEvent_t mid = nullptr);
 // the two halves of launch_accept: row statistics, then decision and sample
