@@ -31,7 +31,8 @@
  *     pointers are read during the call only.  The library keeps no pointer
  *     after it returns and allocates no device memory: the caller passes a
  *     device workspace and a pinned host staging buffer sized by
- *     spec_workspace_bytes().
+ *     spec_workspace_bytes().  Where an automatic split (split_kv = 0) does
+ *     not fit them, one of fewer, longer pieces runs if it does.
  *   - `stream` is a hipStream_t (NULL = the null stream).  All device work
  *     is enqueued on it in order; nothing synchronises the device.  Outputs
  *     are valid once the stream has passed the call.

@@ -541,7 +541,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
         blk = std::max<int64_t>(blk, (int64_t)q.nseg * q.nq * Hq * D * 4);
         stream_bytes = std::max<int64_t>(stream_bytes, rows * q.nseg * D * 4);
       }
-      P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) && 
+      P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) &&
                 stream_bytes <= fuse_max_bytes(attn->split_kv > 0 || streams >= slots ? kFuseMaxBytes : 0);
     }
   }
@@ -701,6 +701,13 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
   Plan P;
   spec_status_t st = build_plan(req, attn, acc, P, mode.coarse);
   if (st != SPEC_OK) return st;
+  // A workspace kept from another batch may hold the longer pieces' partials
+  // and not the short ones' (a batch of few streams has more of them).
+  if (attn && attn->split_kv <= 0 && !mode.coarse &&
+      (ws_bytes < P.device_bytes || staging_bytes < P.plan_bytes)) {
+    P = Plan();
+    if ((st = build_plan(req, attn, acc, P, true)) != SPEC_OK) return st;
+  }
   if (!ws || (reinterpret_cast<uintptr_t>(ws) % kAlign) || ws_bytes < P.device_bytes) return SPEC_ERR_WORKSPACE;
   if (!staging || staging_bytes < P.plan_bytes) return SPEC_ERR_WORKSPACE;
 

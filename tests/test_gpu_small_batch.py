@@ -70,6 +70,35 @@ def test_step_on_one_or_two_streams(gpu_lib, ctx):
         assert np.array_equal(want[key], got[key]), key
 
 
+@pytest.mark.gpu
+def test_workspace_kept_from_another_batch(gpu_lib):
+    """A workspace and a staging buffer that hold four pieces per stream, not
+    the 47 that the automatic split cuts: longer pieces run in them,
+    and nothing is written past their ends."""
+    print("[small] kept workspace", flush=True)
+    pool = U.custom_pool(ctx=[3000], k=[4], Hq=32, Hkv=8, seed=9)
+    b = DeviceBatch(pool, "cuda")
+    ref, bound = reference_and_bound(pool, P_REL)
+    a = b.attn_args()
+    a.split_kv = 768
+    req = b.requests()
+    st, dev, host = B.spec_workspace_bytes(req, a, None)
+    B.check(st, "workspace of four pieces")
+    a.split_kv = 0
+    st, dev0, host0 = B.spec_workspace_bytes(req, a, None)
+    B.check(st, "workspace of the automatic split")
+    assert dev < dev0 and host < host0
+    ws = torch.full((dev + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    staging = torch.full((host + 4096,), 0xA5, dtype=torch.uint8, pin_memory=True)
+    assert ws.data_ptr() % 256 == 0
+    b.out.fill_(float("nan"))
+    stream = torch.cuda.current_stream().cuda_stream
+    B.check(B.spec_verify_attn(req, a, ws.data_ptr(), dev, staging.data_ptr(), host, stream), "kept workspace")
+    torch.cuda.synchronize()
+    assert (np.abs(b.out.cpu().numpy() - ref) <= bound).all()
+    assert bool((ws[dev:] == 0xA5).all()) and bool((staging[host:] == 0xA5).all())
+
+
 @pytest.mark.skipif(torch.cuda.is_available(), reason="made-up device pointers: only where nothing can be launched")
 def test_noalloc_plans_coarser_before_it_refuses():
     """A step whose automatic split needs more than the static scratch, and
