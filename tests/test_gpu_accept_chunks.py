@@ -6,6 +6,7 @@ import pytest
 
 import parity_util as U
 from oracle import verify_accept
+from paper_2505_17074_amd import binding as B
 from paper_2505_17074_amd import workload as W
 from paper_2505_17074_amd.batch import DeviceBatch, Verifier, pad_vocab_rows
 
@@ -34,3 +35,20 @@ def test_chunk_folds(gpu_lib, V, logit, kw):
                             dtype=logit, tree_parent=pool.tree_parent, tree_parents=pool.tree_parents)
         bad, ties = U.compare_accept(v.results(), ref, pool)
         assert not bad and ties <= 1, (bad, ties)
+
+
+@pytest.mark.parametrize("V,logit,parents", [(65537, W.F32, [-1, 0, 0, 1, 1]), (131073, W.BF16, [-1, 0, 0, 0]),
+                                             (6000, W.F32, W.full_binary_tree_parents(2, 5).tolist() + [15])])
+def test_sequential_chunk_folds(gpu_lib, V, logit, parents):
+    """The sequential walk's folds: 17 and 33 chunks, 32 verify positions."""
+    print(f"[chunks] sequential V {V} {logit} {len(parents)} nodes", flush=True)
+    pool = U.custom_pool(ctx=[1] * 3, Hq=1, Hkv=1, d=64, V=V, logit=logit, sigma=2.0, seed=V % 97, tree_parent=parents)
+    b = DeviceBatch(pool, "cuda")
+    pad_vocab_rows(b)
+    v = Verifier(b)
+    v.acc.tree_rule = B.SPEC_TREE_SEQUENTIAL
+    v.run("accept")
+    ref = verify_accept(pool.target_logits, pool.draft_probs, pool.draft_tokens, pool.uniforms, pool.n_q,
+                        dtype=logit, tree_parent=pool.tree_parent, tree_rule="sequential")
+    bad, ties = U.compare_accept(v.results(), ref, pool)
+    assert not bad and ties <= 1, (bad, ties)
