@@ -66,9 +66,9 @@
  *     (surplus work-groups >= 0) override the first round and the surplus;
  *     they exist for tests.
  *   - When the verify attention cuts a request's KV range into pieces, a
- *     separate combine kernel follows, or, in batches of more than one round
- *     of work-groups and with a caller's split_kv (bf16 inputs, partial blocks
- *     up to 64 KB per stream), the last piece of each (request, KV head, head
+ *     separate combine kernel follows, or, in batches of more streams than
+ *     half a round of work-groups and with a caller's split_kv (bf16 inputs,
+ *     partial blocks up to 64 KB per stream), the last piece of each (request, KV head, head
  *     group) to finish combines the pieces' partial outputs.  The environment
  *     variable SPEC_FUSED_COMBINE_MAX_BYTES (a byte count) replaces that
  *     choice's limit; the outputs agree either way within the attention

@@ -207,12 +207,15 @@ constexpr int64_t kMaxPiece = SV_MAX_PIECE;
 // that the split kernel's last piece combines itself; above it the separate
 // combine kernel spreads the work over the device.  The last piece reads the
 // block alone, after every other piece of the stream has finished: that pays
-// only while other items keep the device busy, so a one-round plan (fewer
-// streams than slots) never fuses by default.  Measured: the ragged GQA batch
-// (1024 streams, the few split ones <= 55 KB) 5 us shorter fused; one round,
-// fused against separate: 64 x 32K-key streams (295 KB) 158-166 against
-// 152.5 us, 8 streams of 1000 keys in 8 pieces 21.6 against 17.0, 16 streams
-// of 2000 keys (60 rows) in 16 pieces 40 against 19.  The environment variable
+// only while other items keep the device busy, so a plan with at most half as
+// many streams as slots (most of them split) does not fuse by default.
+// Measured: the ragged GQA batch (1024 streams, the few split ones <= 55 KB) 5
+// us shorter fused; one round, fused against separate: 64 x 32K-key streams
+// (295 KB) 158-166 against 152.5 us, 8 streams of 1000 keys in 8 pieces 21.6
+// against 17.0, 16 streams of 2000 keys (60 rows) in 16 pieces 40 against 19;
+// by streams on 512 slots (20 rows, 700 and 500-2000 keys): 128 25.0 against
+// 21.2 and 32.4 against 27.8 us, 256 28.2 / 28.9 and 44.3 / 44.6, 320 33.6 /
+// 37.7 and 50.0 / 52.9, 448 37.8 / 41.0 and 68.2 / 72.9.  The environment variable
 // SPEC_FUSED_COMBINE_MAX_BYTES overrides the limit (tests use it to reach
 // the fused path with any stream).
 constexpr int64_t kFuseMaxBytes = 64 << 10;
@@ -542,7 +545,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
         stream_bytes = std::max<int64_t>(stream_bytes, rows * q.nseg * D * 4);
       }
       P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) &&
-                stream_bytes <= fuse_max_bytes(attn->split_kv > 0 || streams >= slots ? kFuseMaxBytes : 0);
+                stream_bytes <= fuse_max_bytes(attn->split_kv > 0 || 2 * streams > slots ? kFuseMaxBytes : 0);
     }
   }
 

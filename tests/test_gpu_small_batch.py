@@ -25,6 +25,8 @@ CASES = [
     ("three_waves_d64", dict(ctx=[515, 65], k=[8, 2], Hq=8, Hkv=2, d=64)),
     ("four_waves_tree", dict(ctx=[2000], tree_parent=W.full_binary_tree_parents(2, 4), Hq=8, Hkv=2)),
     ("five_waves", dict(ctx=[1500, 90], k=[8, 8], Hq=16, Hkv=2)),
+    ("half_the_slots", dict(ctx=[600, 300] * 16, k=[4] * 32, Hq=32, Hkv=8)),
+    ("over_half_the_slots", dict(ctx=[600, 300] * 16 + [500], k=[4] * 33, Hq=32, Hkv=8)),
     ("many_pieces", dict(ctx=[34000], k=[2], Hq=4, Hkv=1)),
     ("f32_uncut_128", dict(ctx=[123], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
     ("f32_cut_129", dict(ctx=[124], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
