@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "sv_internal.h"
+#include "sv_rules.h"
 
 namespace {
 
@@ -184,25 +185,6 @@ int groups_per_cu(int waves, int layout, bool coarse) {
   return coarse || layout != sv::kAttnF32 ? 2 : std::max(2, 5 - waves);
 }
 
-// Piece length for a stream of L >= 1 keys and a split of s >= 1 keys: the
-// stream cut into ceil(L / s) equal parts, rounded up to 32 keys (a short
-// trailing piece would leave its work-group idle most of the kernel while its
-// partial costs the same).  Every piece but the last has this length.
-int piece_len(int L, int64_t s) {
-  const int64_t n0 = (L + s - 1) / s;
-  return (int)(((L + n0 - 1) / n0 + 31) / 32 * 32);
-}
-
-// Longest piece when there are at least as many streams as slots
-// (piece_lengths below).  A work-group streams about 30 keys per microsecond,
-// so a 4096-key piece started first runs nearly as long as the whole kernel on
-// a 128-request ragged batch (3200 keys per slot on average).  Measured there
-// with run-time claims, attention alone: 2048-key pieces 158 us, 2560 150,
-// 3072 146, 3328-3840 142-143, 4096 155 (and 155 without claims).
-#ifndef SV_MAX_PIECE
-#define SV_MAX_PIECE 3584
-#endif
-constexpr int64_t kMaxPiece = SV_MAX_PIECE;
 // Largest partial block (rows x pieces x d x 4 bytes) of one split stream
 // that the split kernel's last piece combines itself; above it the separate
 // combine kernel spreads the work over the device.  The last piece reads the
@@ -218,7 +200,6 @@ constexpr int64_t kMaxPiece = SV_MAX_PIECE;
 // 37.7 and 50.0 / 52.9, 448 37.8 / 41.0 and 68.2 / 72.9.  The environment variable
 // SPEC_FUSED_COMBINE_MAX_BYTES overrides the limit (tests use it to reach
 // the fused path with any stream).
-constexpr int64_t kFuseMaxBytes = 64 << 10;
 int64_t fuse_max_bytes(int64_t dflt) {
   const char* e = std::getenv("SPEC_FUSED_COMBINE_MAX_BYTES");
   if (!e || !*e) return dflt;
@@ -226,7 +207,6 @@ int64_t fuse_max_bytes(int64_t dflt) {
   const long long v = std::strtoll(e, &end, 10);
   return (end && *end == 0 && v >= 0) ? (int64_t)v : dflt;
 }
-constexpr int64_t kMaxSplit = 1 << 20;
 // Work-groups launched beyond the item count when items are claimed at run
 // time.  Work-group b runs on XCD b % 8, and the XCDs stream at different
 // rates (the slowest 5-10 % below the fastest on ragged batches, the same
@@ -252,77 +232,6 @@ int64_t claim_first_round(int64_t slots) { return env_count("SPEC_ATTN_FIRST_ROU
 int64_t claim_extra(int64_t n_items) {
   return env_count("SPEC_ATTN_EXTRA_WG", (n_items / 6 + 7) / 8 * 8, 0);
 }
-// Keys per piece of each request's streams (every KV head and head group of
-// a request has the same length).  `slots` = work-groups the device runs at
-// once; `len[i]` = keys of request i, each the length of `mult[i]` streams.
-//  - At least as many streams as slots: pieces of at most kMaxPiece keys
-//    (above) and at least 40 * rows, so that the fp32 partials (rows x d x 4
-//    bytes, written once and read once by the combine) stay a few percent of
-//    the K/V bytes a piece streams; dispatched longest first, the items past
-//    the first round claimed at run time.
-//  - Fewer streams than slots: every work-group takes exactly one item (a
-//    second, nearly empty round of items ran 7-27% slower), and the pieces
-//    are cut so that the longest is as short as the slots allow: one piece
-//    per stream to start with, then repeatedly one more piece for the
-//    request whose pieces are currently longest, while its streams' extra
-//    items still fit the slots.  Every work-group streams at about the same
-//    rate, so the longest piece sets the kernel's end; the slots would
-//    otherwise idle, so pieces may be as short as 128 bytes per column (64
-//    bf16 keys) and 2 * rows keys.  Shorter ones lose to their partials and
-//    start-up: one request of 1000 keys x 8 KV heads (20 rows) 32-key pieces
-//    16.3 us, 64 14.8, 128 16.0, 256 19, whole 33.9; 4000 keys at 72 rows:
-//    64-key pieces 24.1, 128-256 21.3-21.9, 512 25.6, 2000 109.  Where no
-//    stream is longer than 512 bytes per column (256 bf16 keys) the combine
-//    launch costs more than a cut saves (205 keys: whole 13.6, cut 14.4; 300
-//    keys: whole 16.6, cut 14.9).
-// `coarse` (a caller's fixed scratch is too small for this): pieces of at
-// least 40 * rows and 256 keys.
-std::vector<int> piece_lengths(const std::vector<int>& len, const std::vector<int>& mult, int rows_max, int elem,
-                               int64_t slots, bool coarse) {
-  slots = std::max<int64_t>(slots, 1);
-  const size_t B = len.size();
-  std::vector<int> out(B);
-  int64_t streams = 0;
-  for (size_t i = 0; i < B; ++i) streams += mult[i];
-  if (streams >= slots) {
-    for (size_t i = 0; i < B; ++i) out[i] = piece_len(len[i], std::max(kMaxPiece, 40 * (int64_t)rows_max));
-    return out;
-  }
-  const int longest = *std::max_element(len.begin(), len.end());
-  if (!coarse && (int64_t)longest * elem <= 512) {
-    for (size_t i = 0; i < B; ++i) out[i] = piece_len(len[i], kMaxSplit);
-    return out;
-  }
-  int64_t lo = coarse ? std::max<int64_t>(40 * (int64_t)rows_max, 256)
-                      : std::max<int64_t>(2 * (int64_t)rows_max, 128 / elem);
-  lo = std::min<int64_t>((lo + 31) / 32 * 32, kMaxSplit);
-  // greedy: a max-heap of (current piece length, request)
-  std::vector<int64_t> n(B, 1);
-  auto cur = [&](size_t i) { return ((int64_t)len[i] + n[i] - 1) / n[i]; };
-  std::vector<std::pair<int64_t, size_t>> heap;
-  heap.reserve(B);
-  for (size_t i = 0; i < B; ++i) heap.emplace_back(cur(i), i);
-  std::make_heap(heap.begin(), heap.end());
-  int64_t total = streams;
-  while (!heap.empty()) {
-    std::pop_heap(heap.begin(), heap.end());
-    const size_t i = heap.back().second;
-    heap.pop_back();
-    // one more piece for request i: its pieces must stay >= lo keys, and its
-    // streams' extra items must fit the remaining slots
-    if (((int64_t)len[i] + n[i]) / (n[i] + 1) < lo || total + mult[i] > slots) break;
-    ++n[i];
-    total += mult[i];
-    heap.emplace_back(cur(i), i);
-    std::push_heap(heap.begin(), heap.end());
-  }
-  for (size_t i = 0; i < B; ++i) {
-    const int64_t piece = (cur(i) + 31) / 32 * 32;            // equal 32-aligned pieces
-    out[i] = (int)std::min<int64_t>(std::max<int64_t>(piece, 32), kMaxSplit);
-  }
-  return out;
-}
-
 // `coarse`: fewer, longer pieces (less partial scratch), for a caller whose
 // scratch is fixed and too small for the automatic split.
 spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
@@ -434,7 +343,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
     P.kv_bytes = 2 * P.Nkv * Hkv * D * elem;
     const int rmax = sv::max_rows_per_item(P.layout);
     // query-head groups per request so that heads * n_i <= rmax
-    std::vector<int> groups(P.B), hpg(P.B), len(P.B), mult(P.B);
+    std::vector<int> groups(P.B), hpg(P.B), len(P.B), mult(P.B), out_rows(P.B);
     int rows_max = 1;
     for (int i = 0; i < P.B; ++i) {
       const int n = P.reqs[i].nq;
@@ -444,15 +353,17 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
       groups[i] = (G + hpg[i] - 1) / hpg[i];
       len[i] = P.reqs[i].ctx + n;
       mult[i] = Hkv * groups[i];
+      out_rows[i] = n * Hq;
       rows_max = std::max(rows_max, hpg[i] * n);
     }
     const int64_t slots = (int64_t)device_cus() * groups_per_cu((rows_max + 15) / 16, P.layout, coarse);
     std::vector<int> plen;
     if (attn->split_kv > 0) {
       plen.resize(P.B);
-      for (int i = 0; i < P.B; ++i) plen[i] = piece_len(len[i], attn->split_kv);
+      for (int i = 0; i < P.B; ++i) plen[i] = sv::piece_len(len[i], attn->split_kv);
     } else {
-      plen = piece_lengths(len, mult, rows_max, (int)elem, slots, coarse);
+      const sv::CutShape shape{rows_max, Hkv, D, (int)elem, slots, device_cus()};
+      plen = sv::piece_lengths(len, mult, out_rows, shape, coarse);
     }
     P.split = 0;
     for (int i = 0; i < P.B; ++i) P.split = std::max(P.split, plen[i]);
@@ -545,7 +456,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
         stream_bytes = std::max<int64_t>(stream_bytes, rows * q.nseg * D * 4);
       }
       P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) &&
-                stream_bytes <= fuse_max_bytes(attn->split_kv > 0 || 2 * streams > slots ? kFuseMaxBytes : 0);
+                stream_bytes <= fuse_max_bytes(attn->split_kv > 0 || 2 * streams > slots ? sv::kFuseMaxBytes : 0);
     }
   }
 

@@ -1,0 +1,166 @@
+// The planner's rules on sizes: how a batch's streams are cut into pieces.
+// Plain host code, without the HIP runtime, so that the CPU tests compile it
+// by itself.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <utility>
+#include <vector>
+
+namespace sv {
+
+// Piece length for a stream of L >= 1 keys and a split of s >= 1 keys: the
+// stream cut into ceil(L / s) equal parts, rounded up to 32 keys (a short
+// trailing piece would leave its work-group idle most of the kernel while its
+// partial costs the same).  Every piece but the last has this length.
+inline int piece_len(int L, int64_t s) {
+  const int64_t n0 = (L + s - 1) / s;
+  return (int)(((L + n0 - 1) / n0 + 31) / 32 * 32);
+}
+
+// Longest piece when there are at least as many streams as slots
+// (piece_lengths below).  A work-group streams about 30 keys per microsecond,
+// so a 4096-key piece started first runs nearly as long as the whole kernel on
+// a 128-request ragged batch (3200 keys per slot on average).  Measured there
+// with run-time claims, attention alone: 2048-key pieces 158 us, 2560 150,
+// 3072 146, 3328-3840 142-143, 4096 155 (and 155 without claims).
+#ifndef SV_MAX_PIECE
+#define SV_MAX_PIECE 3584
+#endif
+constexpr int64_t kMaxPiece = SV_MAX_PIECE;
+constexpr int64_t kMaxSplit = 1 << 20;
+
+// What the cut depends on, for the whole batch.
+struct CutShape {
+  int rows_max;        // query rows of the widest work item
+  int kv_heads;
+  int d;               // head dim
+  int elem;            // bytes per K/V element
+  int64_t slots;       // work-groups the device runs at once
+  int64_t cus;         // compute units
+};
+
+// Largest partial block (rows x pieces x d x 4 bytes) of one split stream that
+// the bf16 split kernel's last piece combines itself by default.
+constexpr int64_t kFuseMaxBytes = 64 << 10;
+
+// The estimates below were fitted to 1398 calls of uniform batches (8 to 256
+// streams of 130 to 64000 keys, 5 to 72 rows, d = 64 and 128, bf16 and fp32,
+// whole and in 2 to 512 pieces): 4 % RMS of the call's time, and the plan of
+// least estimate is 0.4 % slower than the best one measured on average, 11 %
+// at worst (8 streams of 300 keys, d = 64: 13.5 against 12.2 us).
+
+// Microseconds of one round of work-groups: its longest piece at a
+// work-group's own rate, or the batch's K and V at the HBM rate; where the two
+// are close both show (the fourth-power mean).  A bf16 work-group takes 25 ns
+// a key at d = 128 and 17 at d = 64 whatever its rows, an fp32 one 78 and 42;
+// two fp32 ones of several waves on a compute unit run at 0.6 of that each.
+inline double round_us(const CutShape& c, int64_t longest, int64_t kv_keys, int64_t items) {
+  double ns = c.elem == 4 ? (c.d == 64 ? 42.0 : 78.0) : (c.d == 64 ? 17.0 : 25.0);
+  if (c.elem == 4 && c.rows_max > 16 && items > c.cus) ns *= 1.6;
+  const double own = 1e-3 * ns * (double)longest, all = (double)kv_keys * (2.0 * c.d * c.elem) / 7.0e6;
+  const double a = own * own, b = all * all;
+  return std::sqrt(std::sqrt(a * a + b * b));
+}
+// Microseconds that cut streams cost beside it: the combine's launch, its
+// waves (one per output row of the batch), the partial rows written and read,
+// the walk over one row's pieces, and the further items (laid out and staged
+// by the host, fetched by the device).  2 pieces a stream of 130 keys cost 3 us
+// over 40 output rows, 8 over 8000 and 17 over 18000; 64000 keys of one stream
+// in 63 / 125 / 250 / 500 pieces 43 / 37 / 43 / 66 us.  The combine inside
+// the split kernel (batches of half a round of streams and more, blocks
+// within kFuseMaxBytes) hides its start as far as the other streams cover it:
+// over the separate one 1 us at 256 streams of 512 slots, 2 at 320, 4 from
+// 384 on.
+inline double cut_us(const CutShape& c, int64_t streams, int64_t items, int64_t out_rows, int64_t part_rows,
+                     int64_t nseg_max) {
+  const bool fused = c.elem == 2 && 2 * streams >= c.slots && 2ll * c.rows_max * c.d * 4 <= kFuseMaxBytes;
+  const double busy = fused ? std::min(3.0 * (double)streams / (double)c.slots - 1.25, 1.0) : 0.0;
+  return (3.0 + 0.35e-3 * (double)out_rows) * (1.0 - busy) + 0.4e-6 * (double)part_rows * (c.d * 4.0) +
+         0.085 * (double)nseg_max + 0.003 * (double)(items - streams);
+}
+
+// Keys per piece of each request's streams (every KV head and head group of
+// a request has the same length).  `len[i]` = keys of request i, each the
+// length of `mult[i]` streams, `out_rows[i]` = its (verify position, query
+// head) rows.
+//  - At least as many streams as slots: pieces of at most kMaxPiece keys
+//    (above) and at least 40 * rows, so that the fp32 partials (rows x d x 4
+//    bytes, written once and read once by the combine) stay a few percent of
+//    the K/V bytes a piece streams; dispatched longest first, the items past
+//    the first round claimed at run time.
+//  - Fewer streams than slots: every work-group takes exactly one item (a
+//    second, nearly empty round of items ran 7-27% slower).  One piece per
+//    stream to start with, then repeatedly one more piece for the request
+//    whose pieces are currently longest, while its streams' extra items still
+//    fit the slots and its pieces keep 128 bytes per column (64 bf16 keys) and
+//    2 * rows keys; of the plans on that path the one of the least estimated
+//    time (round_us + cut_us) runs.  What a cut saves is the longest whole
+//    stream's time beyond the longest piece's, and where every stream is short
+//    that is less than the combine costs: 16 requests x 8 KV heads of 64 rows,
+//    261 keys whole 15.6 us, cut in two 22.9, 1000 keys 33.0 / 31.7, 4000
+//    101 / 66; 60 requests of 72 rows and 1000 keys (480 streams: only a few
+//    have a slot for a second piece) 49 / 57.
+// `coarse` (a caller's fixed scratch is too small for this): pieces of at
+// least 40 * rows and 256 keys.
+inline std::vector<int> piece_lengths(const std::vector<int>& len, const std::vector<int>& mult,
+                                      const std::vector<int>& out_rows, const CutShape& c, bool coarse) {
+  const int64_t slots = std::max<int64_t>(c.slots, 1);
+  const size_t B = len.size();
+  std::vector<int> out(B);
+  int64_t streams = 0, kv_keys = 0, rows = 0;
+  for (size_t i = 0; i < B; ++i) {
+    streams += mult[i];
+    kv_keys += (int64_t)len[i] * c.kv_heads;   // head groups of one KV head share its rows
+    rows += out_rows[i];
+  }
+  if (streams >= slots) {
+    for (size_t i = 0; i < B; ++i) out[i] = piece_len(len[i], std::max(kMaxPiece, 40 * (int64_t)c.rows_max));
+    return out;
+  }
+  int64_t lo = coarse ? std::max<int64_t>(40 * (int64_t)c.rows_max, 256)
+                      : std::max<int64_t>(2 * (int64_t)c.rows_max, 128 / c.elem);
+  lo = std::min<int64_t>((lo + 31) / 32 * 32, kMaxSplit);
+  // greedy: a max-heap of (current piece length, request)
+  std::vector<int64_t> n(B, 1);
+  auto cur = [&](size_t i) { return ((int64_t)len[i] + n[i] - 1) / n[i]; };
+  std::vector<std::pair<int64_t, size_t>> heap;
+  heap.reserve(B);
+  for (size_t i = 0; i < B; ++i) heap.emplace_back(cur(i), i);
+  std::make_heap(heap.begin(), heap.end());
+  std::vector<size_t> steps;                 // the request of each further piece
+  size_t best_steps = 0;
+  double best = round_us(c, heap.front().first, kv_keys, streams);
+  int64_t total = streams, part_rows = 0, nseg_max = 1;
+  while (!heap.empty()) {
+    std::pop_heap(heap.begin(), heap.end());
+    const size_t i = heap.back().second;
+    heap.pop_back();
+    // one more piece for request i: its pieces must stay >= lo keys, and its
+    // streams' extra items must fit the remaining slots
+    if (((int64_t)len[i] + n[i]) / (n[i] + 1) < lo || total + mult[i] > slots) break;
+    part_rows += (n[i] == 1 ? 2 : 1) * (int64_t)out_rows[i];
+    nseg_max = std::max(nseg_max, ++n[i]);
+    total += mult[i];
+    heap.emplace_back(cur(i), i);
+    std::push_heap(heap.begin(), heap.end());
+    steps.push_back(i);
+    const double us = round_us(c, (heap.front().first + 31) / 32 * 32, kv_keys, total) +
+                      cut_us(c, streams, total, rows, part_rows, nseg_max);
+    if (coarse || us < best) {
+      best = us;
+      best_steps = steps.size();
+    }
+  }
+  std::fill(n.begin(), n.end(), 1);
+  for (size_t s = 0; s < best_steps; ++s) ++n[steps[s]];
+  for (size_t i = 0; i < B; ++i) {
+    const int64_t piece = (cur(i) + 31) / 32 * 32;            // equal 32-aligned pieces
+    out[i] = (int)std::min<int64_t>(std::max<int64_t>(piece, 32), kMaxSplit);
+  }
+  return out;
+}
+
+}  // namespace sv

@@ -18,8 +18,8 @@ from test_gpu_f32_attn import reference_and_bound
 # bf16 probabilities are carried in two bf16 parts (a relative 2^-17)
 P_REL = 2.0 ** -17
 CASES = [
-    ("uncut_256", dict(ctx=[251, 3], k=[4, 4], Hq=4, Hkv=4)),
-    ("cut_257", dict(ctx=[252, 3], k=[4, 4], Hq=4, Hkv=4)),
+    ("uncut_228", dict(ctx=[223, 3], k=[4, 4], Hq=4, Hkv=4)),
+    ("cut_229", dict(ctx=[224, 3], k=[4, 4], Hq=4, Hkv=4)),
     ("k0_one_row", dict(ctx=[700], k=[0], Hq=2, Hkv=2)),
     ("two_waves", dict(ctx=[1000], k=[4], Hq=8, Hkv=2)),
     ("three_waves_d64", dict(ctx=[515, 65], k=[8, 2], Hq=8, Hkv=2, d=64)),
@@ -28,8 +28,8 @@ CASES = [
     ("half_the_slots", dict(ctx=[600, 300] * 16, k=[4] * 32, Hq=32, Hkv=8)),
     ("over_half_the_slots", dict(ctx=[600, 300] * 16 + [500], k=[4] * 33, Hq=32, Hkv=8)),
     ("many_pieces", dict(ctx=[34000], k=[2], Hq=4, Hkv=1)),
-    ("f32_uncut_128", dict(ctx=[123], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
-    ("f32_cut_129", dict(ctx=[124], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
+    ("f32_uncut_141", dict(ctx=[136], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
+    ("f32_cut_142", dict(ctx=[137], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
 ]
 
 
@@ -75,7 +75,7 @@ def test_step_on_one_or_two_streams(gpu_lib, ctx):
 @pytest.mark.gpu
 def test_workspace_kept_from_another_batch(gpu_lib):
     """A workspace and a staging buffer that hold four pieces per stream, not
-    the 47 that the automatic split cuts: longer pieces run in them,
+    the 24 that the automatic split cuts: longer pieces run in them,
     and nothing is written past their ends."""
     print("[small] kept workspace", flush=True)
     pool = U.custom_pool(ctx=[3000], k=[4], Hq=32, Hkv=8, seed=9)
@@ -106,7 +106,7 @@ def test_noalloc_plans_coarser_before_it_refuses():
     """A step whose automatic split needs more than the static scratch, and
     whose longer pieces fit it, is not refused for its size."""
     n, k = 100, 9
-    req = B.make_requests(np.full(n, 3000), np.full(n, k))
+    req = B.make_requests(np.full(n, 12000), np.full(n, k))
     a = B.SpecAttnArgs()
     a.num_q_heads, a.num_kv_heads, a.head_dim, a.dtype = 8, 1, 128, B.SPEC_BF16
     a.q = a.k = a.v = a.out = 1 << 20

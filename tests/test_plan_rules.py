@@ -1,0 +1,58 @@
+"""The attention planner's choices, read off spec_workspace_bytes on a host
+without a GPU (the rules then assume 256 compute units): a plan that cuts no
+stream needs no partial rows, one that cuts every stream in n pieces at least
+n partial rows of d + 2 floats per query row and head."""
+import numpy as np
+import pytest
+
+from paper_2505_17074_amd import binding as B
+
+
+def sizes(ctx, k, hq, hkv, d, dtype=B.SPEC_BF16, split=0):
+    """(device bytes, bytes of one partial row per query row and head)."""
+    ctx = np.asarray(ctx)
+    req = B.make_requests(ctx, np.full(len(ctx), k))
+    a = B.SpecAttnArgs()
+    a.num_q_heads, a.num_kv_heads, a.head_dim, a.dtype, a.split_kv = hq, hkv, d, dtype, split
+    a.q = a.k = a.v = a.out = 1 << 20
+    a.q_stride_tok, a.q_stride_head, a.kv_stride_tok, a.kv_stride_head = hq * d, d, hkv * d, d
+    st, dev, _ = B.spec_workspace_bytes(req, a, None)
+    B.check(st, "spec_workspace_bytes")
+    return dev, len(ctx) * (k + 1) * hq * (d + 2) * 4
+
+
+# requests, keys, k, query heads, KV heads, d; measured whole and cut in us
+WHOLE = [
+    (16, 261, 7, 64, 8, 128),      # 64 rows: 15.6 whole, 22.9 in two pieces
+    (16, 409, 8, 64, 8, 128),      # 72 rows: 19.6, 26.3
+    (16, 600, 7, 64, 8, 64),       # d = 64: 17.1, 20.5
+    (16, 300, 4, 32, 8, 64),       # 20 rows: 11.8, 16.8
+    (32, 1000, 8, 64, 8, 128),     # 256 streams: 36.7, 45.4
+    (60, 1000, 8, 64, 8, 128),     # 480 streams, few of which have a free slot: 49, 57
+    (1, 200, 4, 32, 8, 128),       # one request: 13.9, 14.3
+]
+CUT = [
+    (1, 1000, 4, 32, 8, 128, 8),   # 34.1 whole, 16.2 in eight pieces
+    (16, 4000, 7, 64, 8, 128, 2),  # 101, 66
+    (32, 4000, 4, 32, 8, 64, 2),
+    (1, 64000, 4, 8, 1, 128, 40),  # one stream: 43 us in 63 pieces, 37 in 125
+]
+
+
+@pytest.mark.parametrize("n,keys,k,hq,hkv,d", WHOLE)
+def test_short_streams_run_whole(n, keys, k, hq, hkv, d):
+    dev, row = sizes([keys - k - 1] * n, k, hq, hkv, d)
+    assert dev < row                                  # the plan's tables alone
+
+
+@pytest.mark.parametrize("n,keys,k,hq,hkv,d,pieces", CUT)
+def test_long_streams_are_cut(n, keys, k, hq, hkv, d, pieces):
+    dev, row = sizes([keys - k - 1] * n, k, hq, hkv, d)
+    assert dev >= pieces * row
+
+
+def test_one_stream_is_not_cut_into_more_pieces_than_pay():
+    """64000 keys on one KV head: 125 pieces 37 us, 500 (as many as there are
+    slots) 66, since the combine walks a row's pieces in turn."""
+    dev, row = sizes([64000 - 5], 4, 8, 1, 128)
+    assert dev < 256 * row
