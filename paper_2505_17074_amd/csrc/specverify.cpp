@@ -185,21 +185,9 @@ int groups_per_cu(int waves, int layout, bool coarse) {
   return coarse || layout != sv::kAttnF32 ? 2 : std::max(2, 5 - waves);
 }
 
-// Largest partial block (rows x pieces x d x 4 bytes) of one split stream
-// that the split kernel's last piece combines itself; above it the separate
-// combine kernel spreads the work over the device.  The last piece reads the
-// block alone, after every other piece of the stream has finished: that pays
-// only while other items keep the device busy, so a plan with at most half as
-// many streams as slots (most of them split) does not fuse by default.
-// Measured: the ragged GQA batch (1024 streams, the few split ones <= 55 KB) 5
-// us shorter fused; one round, fused against separate: 64 x 32K-key streams
-// (295 KB) 158-166 against 152.5 us, 8 streams of 1000 keys in 8 pieces 21.6
-// against 17.0, 16 streams of 2000 keys (60 rows) in 16 pieces 40 against 19;
-// by streams on 512 slots (20 rows, 700 and 500-2000 keys): 128 25.0 against
-// 21.2 and 32.4 against 27.8 us, 256 28.2 / 28.9 and 44.3 / 44.6, 320 33.6 /
-// 37.7 and 50.0 / 52.9, 448 37.8 / 41.0 and 68.2 / 72.9.  The environment variable
-// SPEC_FUSED_COMBINE_MAX_BYTES overrides the limit (tests use it to reach
-// the fused path with any stream).
+// The limit on a fused combine's partial blocks (sv_rules.h).  The environment
+// variable SPEC_FUSED_COMBINE_MAX_BYTES overrides it (tests use it to reach the
+// fused path with any stream).
 int64_t fuse_max_bytes(int64_t dflt) {
   const char* e = std::getenv("SPEC_FUSED_COMBINE_MAX_BYTES");
   if (!e || !*e) return dflt;
@@ -446,17 +434,19 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
     // piece to finish) when the stream's combine weights fit its LDS: rows x
     // (pieces + 1) floats.  Otherwise the split combine kernel runs after it.
     if (bf && part > 0) {
-      int64_t lds = 0, blk = 0, stream_bytes = 0;
+      int64_t lds = 0, blk = 0, stream_bytes = 0, nseg_max = 0;
       for (int i = 0; i < P.B; ++i) {
         const ReqInfo& q = P.reqs[i];
         if (q.nseg <= 1) continue;
         const int64_t rows = (int64_t)hpg[i] * q.nq;
+        nseg_max = std::max<int64_t>(nseg_max, q.nseg);
         lds = std::max<int64_t>(lds, rows * (2 * (int64_t)q.nseg + 1) * 4);
         blk = std::max<int64_t>(blk, (int64_t)q.nseg * q.nq * Hq * D * 4);
         stream_bytes = std::max<int64_t>(stream_bytes, rows * q.nseg * D * 4);
       }
+      const bool fuse = attn->split_kv > 0 || sv::fuse_by_default(streams, slots, nseg_max, stream_bytes);
       P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) &&
-                stream_bytes <= fuse_max_bytes(attn->split_kv > 0 || 2 * streams > slots ? sv::kFuseMaxBytes : 0);
+                stream_bytes <= fuse_max_bytes(fuse ? sv::kFuseMaxBytes : 0);
     }
   }
 

@@ -43,8 +43,29 @@ struct CutShape {
 };
 
 // Largest partial block (rows x pieces x d x 4 bytes) of one split stream that
-// the bf16 split kernel's last piece combines itself by default.
+// the bf16 split kernel's last piece combines itself by default; above it the
+// separate combine kernel spreads the work over the device.
 constexpr int64_t kFuseMaxBytes = 64 << 10;
+// Whether the bf16 split kernel combines its partials itself.  The last piece
+// reads the block alone, after every other piece of the stream has finished:
+// that pays only while other streams' items keep the device busy, so from half
+// as many streams as slots on, and from three eighths on where the block is
+// short (two pieces, or 6 KB).  Measured on one plan each, us fused minus
+// separate over batches of equal and ragged lengths (64-16000 keys, d = 64 and
+// 128; blocks over 64 KB left out), by streams on 512 slots:
+//   rows     128           192            256            320            384
+//   5    +0.5 .. +5.9   -1.8 .. +3.6   -2.2 .. +1.2   -4.0 .. +0.1   -4.4 .. -0.1
+//   16   +2.9 .. +8.4   -1.1 .. +4.1   -0.8 .. +1.6   -1.1 .. +1.7   -4.9 .. -2.0
+//   20   +2.1 .. +8.3   -1.5 .. +2.8   -1.3 .. +1.9   -3.9 .. +0.0   -4.8 .. -3.7
+//   40   +0.9 .. +5.8   -2.1 .. +2.4   -3.6 .. +0.7   -2.7 .. -1.5   -6.0 .. -4.7
+//   72   -1.1           -4.9 .. -1.1   -11.6 .. -2.9  -6.7 .. -6.1   -8.5
+// At 192 streams the two-piece plans and the blocks of up to 6 KB are the ones
+// at or below zero (-2.1 .. +0.7; 100-1000 keys in 5 KB blocks +1.2).  The ragged
+// batch with more streams than slots (1024, the few split ones <= 55 KB): -5;
+// few streams: 8 of 1000 keys in 8 pieces +5, 64 of 32K keys (295 KB) +6 to +14.
+inline bool fuse_by_default(int64_t streams, int64_t slots, int64_t nseg_max, int64_t block_bytes) {
+  return 2 * streams >= slots || (8 * streams >= 3 * slots && (nseg_max <= 2 || block_bytes <= 6 << 10));
+}
 
 // The estimates below were fitted to 1398 calls of uniform batches (8 to 256
 // streams of 130 to 64000 keys, 5 to 72 rows, d = 64 and 128, bf16 and fp32,
@@ -76,8 +97,9 @@ inline double round_us(const CutShape& c, int64_t longest, int64_t kv_keys, int6
 // 384 on.
 inline double cut_us(const CutShape& c, int64_t streams, int64_t items, int64_t out_rows, int64_t part_rows,
                      int64_t nseg_max) {
-  const bool fused = c.elem == 2 && 2 * streams >= c.slots && 2ll * c.rows_max * c.d * 4 <= kFuseMaxBytes;
-  const double busy = fused ? std::min(3.0 * (double)streams / (double)c.slots - 1.25, 1.0) : 0.0;
+  const bool fused = c.elem == 2 && fuse_by_default(streams, c.slots, nseg_max, nseg_max * c.rows_max * c.d * 4) &&
+                     2ll * c.rows_max * c.d * 4 <= kFuseMaxBytes;
+  const double busy = fused ? std::min(std::max(3.0 * (double)streams / (double)c.slots - 1.25, 0.0), 1.0) : 0.0;
   return (3.0 + 0.35e-3 * (double)out_rows) * (1.0 - busy) + 0.4e-6 * (double)part_rows * (c.d * 4.0) +
          0.085 * (double)nseg_max + 0.003 * (double)(items - streams);
 }

@@ -56,3 +56,25 @@ def test_one_stream_is_not_cut_into_more_pieces_than_pay():
     slots) 66, since the combine walks a row's pieces in turn."""
     dev, row = sizes([64000 - 5], 4, 8, 1, 128)
     assert dev < 256 * row
+
+
+# requests, keys, k, query heads, KV heads, d; fused combine by default (its
+# arrival counters take workspace)
+FUSED = [
+    (24, 1500, 4, 8, 8, 128, True),     # 192 streams, two pieces, 5 rows: 37.2 us fused, 39.0 separate
+    (24, 1500, 4, 32, 8, 128, True),    # 20 rows, two pieces
+    (32, 2000, 4, 32, 8, 128, True),    # 256 streams, two pieces
+    (16, 2000, 4, 32, 8, 128, False),   # 128 streams
+    (1, 350, 7, 64, 8, 128, False),     # 8 streams in two pieces: 19.1 us fused, 16.5 separate
+    (1, 1000, 4, 32, 8, 128, False),
+]
+
+
+@pytest.mark.parametrize("n,keys,k,hq,hkv,d,fused", FUSED)
+def test_combine_inside_the_split_kernel(monkeypatch, n, keys, k, hq, hkv, d, fused):
+    args = ([keys - k - 1] * n, k, hq, hkv, d)
+    monkeypatch.delenv("SPEC_FUSED_COMBINE_MAX_BYTES", raising=False)
+    dev, row = sizes(*args)
+    assert dev >= 2 * row
+    monkeypatch.setenv("SPEC_FUSED_COMBINE_MAX_BYTES", "0")
+    assert (dev > sizes(*args)[0]) == fused
