@@ -48,6 +48,7 @@ struct Plan {
   int split = 0;
   int64_t split_streams = 0;   // (request, KV head, head group) streams cut into pieces
   bool fused = false;          // the split kernel combines its own partials
+  bool counters = false;       // the workspace holds its arrival counters
   int64_t grid = 0;            // work-groups of the split kernel
   int64_t first_round = 0;     // work-groups that take their own index's item
   bool claim_word = false;     // the workspace holds the claim word
@@ -221,7 +222,11 @@ int64_t claim_extra(int64_t n_items) {
   return env_count("SPEC_ATTN_EXTRA_WG", (n_items / 6 + 7) / 8 * 8, 0);
 }
 // `coarse`: fewer, longer pieces (less partial scratch), for a caller whose
-// scratch is fixed and too small for the automatic split.
+// scratch is fixed and too small for the automatic split.  Its sizes depend on
+// the batch alone and not on what a cut saves: pieces of 40 * rows and 256 keys
+// at least, at most 4096 fp32 query elements an item.  What plan_sizes() below
+// reports covers it, so a workspace sized for one batch holds another's
+// whenever it is as large by that measure.
 spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
                          const spec_accept_args_t* acc, Plan& P, bool coarse = false) {
   spec_status_t st = check_requests(r);
@@ -329,7 +334,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
     const int D = attn->head_dim;
     const int Hq = attn->num_q_heads, Hkv = attn->num_kv_heads, G = Hq / Hkv;
     P.kv_bytes = 2 * P.Nkv * Hkv * D * elem;
-    const int rmax = sv::max_rows_per_item(P.layout);
+    const int rmax = coarse && !bf ? 4096 / D : sv::max_rows_per_item(P.layout);
     // query-head groups per request so that heads * n_i <= rmax
     std::vector<int> groups(P.B), hpg(P.B), len(P.B), mult(P.B), out_rows(P.B);
     int rows_max = 1;
@@ -447,6 +452,8 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
       const bool fuse = attn->split_kv > 0 || sv::fuse_by_default(streams, slots, nseg_max, stream_bytes);
       P.fused = lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) &&
                 stream_bytes <= fuse_max_bytes(fuse ? sv::kFuseMaxBytes : 0);
+      P.counters = P.fused || (coarse && lds <= sv::attn_lds_bytes(D, nr, P.layout) && blk < ((int64_t)1 << 31) &&
+                               stream_bytes <= fuse_max_bytes(sv::kFuseMaxBytes));
     }
   }
 
@@ -479,7 +486,7 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
   P.off_part_ml = off;
   off = align_up(off + sizeof(float) * 2 * (size_t)P.parts);
   P.off_counters = off;                // the fused combine's arrival counters
-  off = align_up(off + sizeof(unsigned long long) * (size_t)(P.fused ? P.split_streams : 0));
+  off = align_up(off + sizeof(unsigned long long) * (size_t)(P.counters ? P.split_streams : 0));
   P.off_claim = off;                   // the split kernel's claim word
   off = align_up(off + (P.claim_word ? sizeof(unsigned long long) : 0));
   P.off_rowstats = off;
@@ -489,6 +496,23 @@ spec_status_t build_plan(const spec_requests_t* r, const spec_attn_args_t* attn,
   P.off_flag = off;                    // debug check result (SPEC_DEBUG_VALIDATE)
   off = align_up(off + (P.has_acc ? sizeof(uint32_t) : 0));
   P.device_bytes = off;
+  return SPEC_OK;
+}
+
+// What a caller's workspace and staging buffer need: the automatic plan's
+// sizes, and the coarse one's where the split is automatic.
+spec_status_t plan_sizes(const spec_requests_t* req, const spec_attn_args_t* attn, const spec_accept_args_t* acc,
+                         size_t* device_bytes, size_t* host_bytes) {
+  Plan P;
+  const spec_status_t st = build_plan(req, attn, acc, P);
+  if (st != SPEC_OK) return st;
+  *device_bytes = P.device_bytes;
+  *host_bytes = P.plan_bytes;
+  Plan Q;
+  if (attn && attn->split_kv <= 0 && build_plan(req, attn, acc, Q, true) == SPEC_OK) {
+    *device_bytes = std::max(*device_bytes, Q.device_bytes);
+    *host_bytes = std::max(*host_bytes, Q.plan_bytes);
+  }
   return SPEC_OK;
 }
 
@@ -831,12 +855,7 @@ extern "C" {
 spec_status_t spec_workspace_bytes(const spec_requests_t* req, const spec_attn_args_t* attn,
                                    const spec_accept_args_t* acc, size_t* device_bytes, size_t* host_bytes) {
   if (!device_bytes || !host_bytes) return SPEC_ERR_INVALID_ARG;
-  Plan P;
-  const spec_status_t st = build_plan(req, attn, acc, P);
-  if (st != SPEC_OK) return st;
-  *device_bytes = P.device_bytes;
-  *host_bytes = P.plan_bytes;
-  return SPEC_OK;
+  return plan_sizes(req, attn, acc, device_bytes, host_bytes);
 }
 
 spec_status_t spec_verify_attn(const spec_requests_t* req, const spec_attn_args_t* attn, void* workspace,

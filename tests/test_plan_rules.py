@@ -78,3 +78,77 @@ def test_combine_inside_the_split_kernel(monkeypatch, n, keys, k, hq, hkv, d, fu
     assert dev >= 2 * row
     monkeypatch.setenv("SPEC_FUSED_COMBINE_MAX_BYTES", "0")
     assert (dev > sizes(*args)[0]) == fused
+
+
+# (requests, longest context) whose sizes a caller allocated, those it is then
+# used for, query heads, KV heads, d, type: shapes whose first batch is now cut
+# less or by other rows than the second one's longer pieces assume
+KEPT = [
+    (16, 15080, 32, 384, 32, 32, 64, B.SPEC_F32),
+    (16, 24482, 8, 26762, 32, 32, 128, B.SPEC_F32),
+    (32, 32438, 128, 163, 64, 8, 128, B.SPEC_F32),
+    (64, 26852, 128, 129, 32, 8, 128, B.SPEC_F32),
+    (8, 3516, 4, 1171, 32, 32, 128, B.SPEC_BF16),
+    (64, 23812, 64, 8799, 16, 4, 64, B.SPEC_BF16),
+    (2, 18799, 32, 2103, 32, 8, 128, B.SPEC_BF16),
+]
+
+
+def batch_args(n, ctx, hq, hkv, d, dtype):
+    req = B.make_requests(np.linspace(max(1, ctx // 16), ctx, n).astype(np.int32), np.full(n, 4))
+    a = B.SpecAttnArgs()
+    a.num_q_heads, a.num_kv_heads, a.head_dim, a.dtype = hq, hkv, d, dtype
+    a.q = a.k = a.v = a.out = 1 << 20
+    a.q_stride_tok, a.q_stride_head, a.kv_stride_tok, a.kv_stride_head = hq * d, d, hkv * d, d
+    return req, a
+
+
+def longer_pieces_bytes(n, ctx, hq, hkv, d, dtype):
+    """Device and staging bytes of the plan of few, long pieces: 512 slots,
+    pieces of max(40 rows, 256) keys (3584 where there are as many streams as
+    slots), the widest item 80 rows (fp32: 4096 / d).  One k for all requests."""
+    req, _ = batch_args(n, ctx, hq, hkv, d, dtype)
+    L, nq, G = [int(req.ctx_len[i]) + 5 for i in range(n)], 5, hq // hkv
+    ng = -(-G // max(1, (80 if dtype == B.SPEC_BF16 else 4096 // d) // nq))
+    hpg = -(-G // ng)
+    mult, rows = hkv * -(-G // hpg), hpg * nq
+    pieces = [1] * n
+    if mult * n >= 512:
+        pieces = [-(-x // 3584) for x in L]
+    else:
+        lo, total = -(-max(40 * rows, 256) // 32) * 32, mult * n
+        while True:
+            i = max(range(n), key=lambda j: (-(-L[j] // pieces[j]), j))
+            if (L[i] + pieces[i]) // (pieces[i] + 1) < lo or total + mult > 512:
+                break
+            pieces[i] += 1
+            total += mult
+    up = lambda x: -(-x // 256) * 256
+    length = [-(-(-(-x // p)) // 32) * 32 for x, p in zip(L, pieces)]
+    pieces = [-(-x // y) for x, y in zip(L, length)]
+    items = sum(pieces) * mult
+    part = sum(p for p in pieces if p > 1) * nq * hq
+    tables = up(32 * n) + up(4 * nq * n) + up(64 * items)
+    return tables + up(part * d * 4) + up(part * 8), tables
+
+
+@pytest.mark.parametrize("na,ca,nb,cb,hq,hkv,d,dtype", KEPT)
+def test_a_kept_workspace_is_not_refused(na, ca, nb, cb, hq, hkv, d, dtype):
+    """The sizes cover the plan of long pieces for the same batch, and a call
+    takes any workspace that holds its own: no device here, so it then fails
+    later (SPEC_ERR_HIP), not for its size."""
+    import torch
+    req, a = batch_args(na, ca, hq, hkv, d, dtype)
+    st, dev, host = B.spec_workspace_bytes(req, a, None)
+    B.check(st, "spec_workspace_bytes")
+    need = longer_pieces_bytes(na, ca, hq, hkv, d, dtype)
+    assert dev >= need[0] and host >= need[1]
+    if torch.cuda.is_available():
+        return                           # made-up device pointers: only where nothing can be launched
+    need = longer_pieces_bytes(nb, cb, hq, hkv, d, dtype)
+    extra = 16384                        # arrival counters (8 bytes a stream) and the claim word
+    if dev < need[0] + extra or host < need[1]:
+        return
+    req, a = batch_args(nb, cb, hq, hkv, d, dtype)
+    staging = np.zeros(host + 256, np.uint8)
+    assert B.spec_verify_attn(req, a, 1 << 20, dev, (staging.ctypes.data + 255) // 256 * 256, host, 0) == B.SPEC_ERR_HIP
