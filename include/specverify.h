@@ -338,9 +338,9 @@ SPEC_API spec_status_t spec_accept(const spec_requests_t* req,
  * side stream (one per device, created on first use at the default priority)
  * that forks from `stream` at the start of the call and is joined back into `stream`
  * before the call returns, overlapping the attention kernels; small steps
- * (up to 128 MiB of keys and values), where the fork and join cost more than
- * they hide, run both parts on `stream`.  Completion is ordered by `stream`
- * alone either way. */
+ * (up to about 165 MiB of keys, values and logits), where the fork and join
+ * cost more than they hide, run both parts on `stream`.  Completion is ordered
+ * by `stream` alone either way. */
 SPEC_API spec_status_t spec_verify(const spec_requests_t* req,
                           const spec_attn_args_t* attn,
                           const spec_accept_args_t* acc,

@@ -528,14 +528,6 @@ struct SideStream {
   hipEvent_t fork = nullptr, join = nullptr;
   bool ready = false;
 };
-// Below this many K/V bytes a step stays on the caller's stream: the fork and
-// join (event packets both queues wait on, and their host calls) cost more
-// than hiding the acceptance under so short an attention saves.  Steps over
-// 512-2048-key contexts, 8 KV heads, one stream against two: 1 request 31
-// against 45-55 us, 4 requests 36 against 50-60, 16 requests (88 MB of K/V)
-// 48 against 58-62, 32 requests (173 MB) 66 against 55-59; 1 request at 32 KV
-// heads 32 against 44-58.
-constexpr int64_t kOverlapMinBytes = 128 << 20;
 constexpr int kMaxDevices = 64;
 SideStream g_side[kMaxDevices];
 
@@ -830,7 +822,10 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
     return true;
   };
 
-  if (mode.overlap && attn && acc && P.kv_bytes > kOverlapMinBytes) {
+  // logit rows whose statistics the acceptance takes, and one draft row a request
+  const int64_t acc_rows = (P.tree && !P.per_req && c.tree == 1 ? (int64_t)P.B * P.topo.n_inner : P.Nq) + P.B;
+  if (mode.overlap && attn && acc &&
+      sv::overlap_pays(P.kv_bytes, acc_rows * acc->vocab * (acc->dtype == SPEC_BF16 ? 2 : 4))) {
     SideStream* S = side_stream();
     if (!S) return SPEC_ERR_HIP;
     std::lock_guard<std::mutex> lk(S->mu);

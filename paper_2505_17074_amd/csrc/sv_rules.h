@@ -1,4 +1,5 @@
-// The planner's rules on sizes: how a batch's streams are cut into pieces.
+// The planner's rules on sizes: how a batch's streams are cut into pieces, where
+// the pieces are combined, and whether a step runs on one stream or two.
 // Plain host code, without the HIP runtime, so that the CPU tests compile it
 // by itself.
 #pragma once
@@ -183,6 +184,27 @@ inline std::vector<int> piece_lengths(const std::vector<int>& len, const std::ve
     out[i] = (int)std::min<int64_t>(std::max<int64_t>(piece, 32), kMaxSplit);
   }
   return out;
+}
+
+// Whether a step's acceptance runs beside its attention on a second stream.
+// The fork and join (event packets that both queues wait on, and their host
+// calls) cost a step that runs ahead of the device about what hiding the
+// shorter part saves once K/V and 1.2 times the logit bytes pass 165 MiB (the
+// logits weigh more: acceptance streams slower, and its own chain of round
+// trips is hidden too); a caller that waits for each step pays the host calls,
+// 8 to 17 us, at any size.  752 steps on both, 2 to 128 requests, vocabularies
+// of 5000 to 128256, us two streams minus one, mean (calls in a row / waited
+// for), by MiB of K/V and of logits:
+//   K/V        logits 1-4      4-16       16-48       48-120
+//    32       +17 / +17    +17 / +17   +14 / +16    +6 / +14
+//    64       +13 / +15    +12 / +15    +8 / +14    +1 / +12
+//    96        +9 / +14     +7 / +14    +4 / +13    -3 / +11
+//   128        +5 / +14     +2 / +13    -1 / +12    -5 / +10
+//   160         0 / +14     -2 / +13    -4 / +12    -6 / +9
+//   200        -5 / +14     -6 / +13    -7 / +12    -7 / +9
+//   400        -6 / +13     -7 / +12    -7 / +12    -7 / +8
+inline bool overlap_pays(int64_t kv_bytes, int64_t logit_bytes) {
+  return kv_bytes + logit_bytes + logit_bytes / 5 > (int64_t)165 << 20;
 }
 
 }  // namespace sv

@@ -54,11 +54,21 @@ def test_short_pieces(gpu_lib, name, kw):
         assert np.array_equal(paged.results()["out"], out)
 
 
+# requests, context, drafts, vocabulary, whether two streams run: the rule's line at
+# 165 MiB of K/V (8 KB a key here) and 1.2 times the logits, few and many of them
+STEPS = [
+    ("kv_163", 8, 5200, 3, 5000, False),
+    ("kv_169", 8, 5400, 3, 5000, True),
+    ("logits_little", 16, 1500, 8, 32000, False),     # 94 MiB of K/V, 20 of logits
+    ("logits_much", 16, 1500, 8, 128256, True),       # and 78
+]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("ctx", [4000, 4200])       # 125 and 131 MiB of K/V: one stream, two streams
-def test_step_on_one_or_two_streams(gpu_lib, ctx):
-    print(f"[small] step ctx {ctx}", flush=True)
-    pool = U.custom_pool(ctx=[ctx] * 8, k=[3] * 8, Hq=8, Hkv=8, V=5000, seed=5)
+@pytest.mark.parametrize("name,n,ctx,k,V,two", STEPS, ids=[c[0] for c in STEPS])
+def test_step_on_one_or_two_streams(gpu_lib, name, n, ctx, k, V, two):
+    print(f"[small] step {name}", flush=True)
+    pool = U.custom_pool(ctx=[ctx] * n, k=[k] * n, Hq=8, Hkv=8, V=V, seed=5)
     b = DeviceBatch(pool, "cuda")
     v = Verifier(b)
     v.run("attn")
@@ -66,10 +76,16 @@ def test_step_on_one_or_two_streams(gpu_lib, ctx):
     want = v.results()
     for t in (b.out, b.accepted_len, b.next_token, b.accepted_node):
         t.zero_()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()                      # creates the handles
+    v.attn.event_end, v.acc.event_begin = ev[0].cuda_event, ev[1].cuda_event
     v.run("verify")
     got = v.results()
     for key in want:
         assert np.array_equal(want[key], got[key]), key
+    # on one stream the acceptance begins once the attention has ended
+    assert (ev[0].elapsed_time(ev[1]) < 0) == two
 
 
 @pytest.mark.gpu
