@@ -76,11 +76,13 @@ inline bool fuse_by_default(int64_t streams, int64_t slots, int64_t nseg_max, in
 
 // Microseconds of one round of work-groups: its longest piece at a
 // work-group's own rate, or the batch's K and V at the HBM rate; where the two
-// are close both show (the fourth-power mean).  A bf16 work-group takes 25 ns
-// a key at d = 128 and 17 at d = 64 whatever its rows, an fp32 one 78 and 42;
+// are close both show (the fourth-power mean).  A bf16 work-group takes 26 ns
+// a key at d = 128 and 17.5 at d = 64 whatever its rows, an fp32 one 78 and 42;
 // two fp32 ones of several waves on a compute unit run at 0.6 of that each.
+// (Paged caches stream up to a tenth slower; their plan is the packed one's, so
+// that the outputs are the same bits.)
 inline double round_us(const CutShape& c, int64_t longest, int64_t kv_keys, int64_t items) {
-  double ns = c.elem == 4 ? (c.d == 64 ? 42.0 : 78.0) : (c.d == 64 ? 17.0 : 25.0);
+  double ns = c.elem == 4 ? (c.d == 64 ? 42.0 : 78.0) : (c.d == 64 ? 17.5 : 26.0);
   if (c.elem == 4 && c.rows_max > 16 && items > c.cus) ns *= 1.6;
   const double own = 1e-3 * ns * (double)longest, all = (double)kv_keys * (2.0 * c.d * c.elem) / 7.0e6;
   const double a = own * own, b = all * all;
@@ -101,8 +103,8 @@ inline double cut_us(const CutShape& c, int64_t streams, int64_t items, int64_t 
   const bool fused = c.elem == 2 && fuse_by_default(streams, c.slots, nseg_max, nseg_max * c.rows_max * c.d * 4) &&
                      2ll * c.rows_max * c.d * 4 <= kFuseMaxBytes;
   const double busy = fused ? std::min(std::max(3.0 * (double)streams / (double)c.slots - 1.25, 0.0), 1.0) : 0.0;
-  return (3.0 + 0.35e-3 * (double)out_rows) * (1.0 - busy) + 0.4e-6 * (double)part_rows * (c.d * 4.0) +
-         0.085 * (double)nseg_max + 0.003 * (double)(items - streams);
+  return (3.4 + 0.35e-3 * (double)out_rows) * (1.0 - busy) + 0.4e-6 * (double)part_rows * (c.d * 4.0) +
+         0.085 * (double)nseg_max + 0.0015 * (double)(items - streams);
 }
 
 // Keys per piece of each request's streams (every KV head and head group of
@@ -146,16 +148,20 @@ inline std::vector<int> piece_lengths(const std::vector<int>& len, const std::ve
   int64_t lo = coarse ? std::max<int64_t>(40 * (int64_t)c.rows_max, 256)
                       : std::max<int64_t>(2 * (int64_t)c.rows_max, 128 / c.elem);
   lo = std::min<int64_t>((lo + 31) / 32 * 32, kMaxSplit);
-  // greedy: a max-heap of (current piece length, request)
   std::vector<int64_t> n(B, 1);
   auto cur = [&](size_t i) { return ((int64_t)len[i] + n[i] - 1) / n[i]; };
+  const int64_t longest = *std::max_element(len.begin(), len.end());
+  double best = round_us(c, longest, kv_keys, streams);
+  // what no cut plan undercuts: pieces of `lo` keys for no partial rows
+  const bool cut = coarse || round_us(c, std::min(lo, longest), kv_keys, streams) +
+                                     cut_us(c, streams, streams, rows, 0, 2) < best;
+  // greedy: a max-heap of (current piece length, request)
   std::vector<std::pair<int64_t, size_t>> heap;
   heap.reserve(B);
-  for (size_t i = 0; i < B; ++i) heap.emplace_back(cur(i), i);
+  for (size_t i = 0; cut && i < B; ++i) heap.emplace_back(cur(i), i);
   std::make_heap(heap.begin(), heap.end());
   std::vector<size_t> steps;                 // the request of each further piece
   size_t best_steps = 0;
-  double best = round_us(c, heap.front().first, kv_keys, streams);
   int64_t total = streams, part_rows = 0, nseg_max = 1;
   while (!heap.empty()) {
     std::pop_heap(heap.begin(), heap.end());

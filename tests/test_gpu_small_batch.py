@@ -18,8 +18,8 @@ from test_gpu_f32_attn import reference_and_bound
 # bf16 probabilities are carried in two bf16 parts (a relative 2^-17)
 P_REL = 2.0 ** -17
 CASES = [
-    ("uncut_228", dict(ctx=[223, 3], k=[4, 4], Hq=4, Hkv=4)),
-    ("cut_229", dict(ctx=[224, 3], k=[4, 4], Hq=4, Hkv=4)),
+    ("uncut_238", dict(ctx=[233, 3], k=[4, 4], Hq=4, Hkv=4)),
+    ("cut_239", dict(ctx=[234, 3], k=[4, 4], Hq=4, Hkv=4)),
     ("k0_one_row", dict(ctx=[700], k=[0], Hq=2, Hkv=2)),
     ("two_waves", dict(ctx=[1000], k=[4], Hq=8, Hkv=2)),
     ("three_waves_d64", dict(ctx=[515, 65], k=[8, 2], Hq=8, Hkv=2, d=64)),
@@ -28,8 +28,8 @@ CASES = [
     ("half_the_slots", dict(ctx=[600, 300] * 16, k=[4] * 32, Hq=32, Hkv=8)),
     ("over_half_the_slots", dict(ctx=[600, 300] * 16 + [500], k=[4] * 33, Hq=32, Hkv=8)),
     ("many_pieces", dict(ctx=[34000], k=[2], Hq=4, Hkv=1)),
-    ("f32_uncut_141", dict(ctx=[136], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
-    ("f32_cut_142", dict(ctx=[137], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
+    ("f32_uncut_151", dict(ctx=[146], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
+    ("f32_cut_152", dict(ctx=[147], k=[4], Hq=2, Hkv=2, d=64, qkv=W.F32)),
 ]
 
 

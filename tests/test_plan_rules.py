@@ -51,6 +51,22 @@ def test_long_streams_are_cut(n, keys, k, hq, hkv, d, pieces):
     assert dev >= pieces * row
 
 
+# the line the GPU tests of short pieces run on both sides of (test_gpu_small_batch.py)
+EDGES = [
+    ([233, 3], 4, 4, 128, B.SPEC_BF16, False),
+    ([234, 3], 4, 4, 128, B.SPEC_BF16, True),
+    ([146], 2, 2, 64, B.SPEC_F32, False),
+    ([147], 2, 2, 64, B.SPEC_F32, True),
+]
+
+
+@pytest.mark.parametrize("ctx,hq,hkv,d,dtype,cut", EDGES)
+def test_shortest_cut(ctx, hq, hkv, d, dtype, cut):
+    dev, _ = sizes(ctx, 4, hq, hkv, d, dtype)
+    one = 5 * hq * (d + 2) * 4                        # a partial row of the first request's rows and heads
+    assert (dev >= 2 * one) == cut
+
+
 def test_one_stream_is_not_cut_into_more_pieces_than_pay():
     """64000 keys on one KV head: 125 pieces 37 us, 500 (as many as there are
     slots) 66, since the combine walks a row's pieces in turn."""
