@@ -494,42 +494,6 @@ hipError_t launch_tall(const LmhParams& p, hipStream_t s) {
 
 }  // namespace
 
-// Tile shape for M rows and V vocabulary entries, in units of about 14 us at
-// K = 4096:
-//  - low tiles take every row at once (M <= 192); they leave the chip half
-//    empty where the vocabulary has few tiles (M = 160, V = 9000: 70 us
-//    against 56 for 64-row tall tiles);
-//  - tall tiles cost about RB + 3 a round of work-groups over the CUs (the
-//    products, and the prologue, epilogue and slice hand-overs), M = 240 to
-//    960 at V = 32000 within a few percent; rows past M read as zeros and cost
-//    no traffic, so the row tiles are balanced.
-// At M = 110 / 160 / 192, V = 32000: low 68 / 75 / 83 us, tall 78 / 90 / 91.
-LmhGeometry lmh_geometry(int M, int V, int cus) {
-  LmhGeometry g{};
-  const int64_t low_tiles = ((int64_t)V + kLmhNTLow - 1) / kLmhNTLow;
-  if (M <= 64 || (M <= 192 && 2 * low_tiles > cus)) {
-    g.low_wr = M <= 96 ? 1 : 2;
-    g.rb = (M + 16 * g.low_wr - 1) / (16 * g.low_wr);
-    g.m_tiles = 1;
-    g.nt = kLmhNTLow;
-  } else {
-    int64_t best = -1;
-    for (int rb = 1; rb <= 6; ++rb) {
-      const int64_t mt = (M + 64 * rb - 1) / (64 * rb);
-      const int64_t groups = mt * (((int64_t)V + kLmhNT - 1) / kLmhNT);
-      const int64_t cost = (groups + cus - 1) / cus * (rb + 3);
-      if (best < 0 || cost < best) {
-        best = cost;
-        g.rb = rb;
-        g.m_tiles = (int32_t)mt;
-      }
-    }
-    g.nt = kLmhNT;
-  }
-  g.tile_rows = (M + g.m_tiles - 1) / g.m_tiles;
-  return g;
-}
-
 hipError_t launch_lmh(const LmhParams& p, int cus, hipStream_t s) {
   if (p.M < 1 || p.tile_rows < 1 || p.m_tiles != (p.M + p.tile_rows - 1) / p.tile_rows) return hipErrorInvalidValue;
   if (p.low_wr) {

@@ -16,7 +16,6 @@
 #include <vector>
 
 #include "sv_internal.h"
-#include "sv_rules.h"
 
 namespace {
 
@@ -773,7 +772,7 @@ spec_status_t run(const spec_requests_t* req, const spec_attn_args_t* attn, cons
     g.M = (int32_t)P.Nq;
     g.K = lm->hidden_dim;
     g.V = acc->vocab;
-    const sv::LmhGeometry geo = sv::lmh_geometry(g.M, g.V, device_cus());
+    const sv::LmhGeometry geo = sv::lmh_geometry(g.M, g.V, g.K, device_cus());
     g.ntiles = (acc->vocab + geo.nt - 1) / geo.nt;
     g.rb = geo.rb;
     g.low_wr = geo.low_wr;

@@ -5,6 +5,7 @@
 
 #include "../../include/specverify.h"
 #include "sv_attn.h"
+#include "sv_rules.h"
 
 namespace sv {
 
@@ -91,8 +92,6 @@ constexpr int kAccMaxChunks = 1024;    // vocabularies up to 4M entries
 
 // The target model's LM head, logits = hidden . weight^T, with the softmax
 // statistics of each (row, vocabulary tile) taken in the epilogue.
-constexpr int kLmhNT = 256;            // vocabulary entries per work-group and statistics tile: tall tiles
-constexpr int kLmhNTLow = 128;         // and low ones
 struct LmhParams {
   const uint16_t* hidden;   // [M, K] bf16, row stride h_st elements
   const uint16_t* weight;   // [V, K] bf16, row stride w_st elements
@@ -117,13 +116,7 @@ struct LmhParams {
   int32_t nodes_n16;
   int32_t B;
 };
-struct LmhGeometry {
-  int32_t rb, low_wr, tile_rows, m_tiles, nt;   // nt: vocabulary entries per tile
-};
 constexpr int kLmhOffsetRows = 256;    // rows of hidden whose offsets the host keeps below 2^31
-// The tile shape and row tiles for M rows, V vocabulary entries and cus
-// compute units.
-LmhGeometry lmh_geometry(int M, int V, int cus);
 hipError_t launch_lmh(const LmhParams& p, int cus, hipStream_t s);
 // Chunk statistics [Nq, nch] (the decision kernel's input) folded from the
 // LM head's tile statistics, plus the row-statistics kernel's other duties

@@ -1,5 +1,6 @@
-// The planner's rules on sizes: how a batch's streams are cut into pieces, where
-// the pieces are combined, and whether a step runs on one stream or two.
+// The rules on sizes: how a batch's streams are cut into pieces, where the
+// pieces are combined, whether a step runs on one stream or two, and the LM
+// head's tiles.
 // Plain host code, without the HIP runtime, so that the CPU tests compile it
 // by itself.
 #pragma once
@@ -211,6 +212,70 @@ inline std::vector<int> piece_lengths(const std::vector<int>& len, const std::ve
 //   400        -6 / +13     -7 / +12    -7 / +12    -7 / +8
 inline bool overlap_pays(int64_t kv_bytes, int64_t logit_bytes) {
   return kv_bytes + logit_bytes + logit_bytes / 5 > (int64_t)165 << 20;
+}
+
+// The LM head's tiles.
+constexpr int kLmhNT = 256;            // vocabulary entries per work-group and statistics tile: tall tiles
+constexpr int kLmhNTLow = 128;         // and low ones
+struct LmhGeometry {
+  int32_t rb, low_wr, tile_rows, m_tiles, nt;   // 16-row blocks per wave, waves along the rows (0: tall), ...
+};
+// Whether M rows take the low tiles (every row at once against 128 vocabulary
+// entries, one work-group per compute unit that runs on from tile to tile).
+// Measured as low over tall tiles' time, weights from HBM (the cache between
+// the calls full of other reads):
+//  - up to one round of low tiles: tall ones leave half the compute units
+//    without any.  V = 32000, K = 1024 to 8192: M = 20 0.84-0.73, 95 0.97-0.77,
+//    190 1.02-0.89; V = 9000, M = 20 0.78-0.52, 125 0.98-0.80, 160 1.07-0.92.
+//    Weights that stay in the Infinity Cache between calls (256 MB) favour the
+//    tall tiles' cached loads beyond 64 rows: V = 32000, K = 1024, M = 95 1.07, V
+//    = 16000, K = 4096, M = 125 1.08, 160 1.20;
+//  - more rounds, fewer than two for each of the tall tiles': V = 78071, M =
+//    20 0.85-0.79, 95 0.99-0.86, 190 0.99-0.96;
+//  - two for each: their epilogues, and a last round that is partly empty, are
+//    paid twice.  V = 50304, M = 20 1.02-0.98, 40 1.08, 95 1.15, 190 1.27.
+//    Where every round is full and the weights are long they pay later: V =
+//    128256, K = 4096, M = 40 0.99, 60 1.05, 95 1.08; K = 8192, M = 60 0.99,
+//    80 0.93, 95 0.97.
+inline bool lmh_low_tiles(int M, int V, int K, int cus) {
+  const int64_t tiles = ((int64_t)V + kLmhNTLow - 1) / kLmhNTLow;
+  const int64_t rounds = (tiles + cus - 1) / cus;
+  const int64_t tall_rounds = (((int64_t)V + kLmhNT - 1) / kLmhNT + cus - 1) / cus;
+  const int64_t weight_mib = ((int64_t)V * K * 2) >> 20;
+  if (2 * tiles <= cus) return M <= (weight_mib < 140 ? 64 : 128);
+  if (rounds < 2 * tall_rounds) return M <= (weight_mib < 80 ? 64 : 192);
+  if (K < 2048) return M <= 16;
+  if (10 * tiles < 9 * rounds * cus) return M <= 24;
+  return M <= (K >= 6144 ? 96 : K >= 4096 ? 48 : 24);
+}
+// Tile shape for M rows, V vocabulary entries and hidden width K: low tiles as
+// above, or tall ones, which cost about RB + 3 a round of work-groups over the
+// CUs (the products, and the prologue, epilogue and slice hand-overs; M = 240
+// to 960 at V = 32000 within a few percent).  Rows past M read as zeros and
+// cost no traffic, so the row tiles are balanced.
+inline LmhGeometry lmh_geometry(int M, int V, int K, int cus) {
+  LmhGeometry g{};
+  if (lmh_low_tiles(M, V, K, cus)) {
+    g.low_wr = M <= 96 ? 1 : 2;
+    g.rb = (M + 16 * g.low_wr - 1) / (16 * g.low_wr);
+    g.m_tiles = 1;
+    g.nt = kLmhNTLow;
+  } else {
+    int64_t best = -1;
+    for (int rb = 1; rb <= 6; ++rb) {
+      const int64_t mt = (M + 64 * rb - 1) / (64 * rb);
+      const int64_t groups = mt * (((int64_t)V + kLmhNT - 1) / kLmhNT);
+      const int64_t cost = (groups + cus - 1) / cus * (rb + 3);
+      if (best < 0 || cost < best) {
+        best = cost;
+        g.rb = rb;
+        g.m_tiles = (int32_t)mt;
+      }
+    }
+    g.nt = kLmhNT;
+  }
+  g.tile_rows = (M + g.m_tiles - 1) / g.m_tiles;
+  return g;
 }
 
 }  // namespace sv

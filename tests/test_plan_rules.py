@@ -168,3 +168,64 @@ def test_a_kept_workspace_is_not_refused(na, ca, nb, cb, hq, hkv, d, dtype):
     req, a = batch_args(nb, cb, hq, hkv, d, dtype)
     staging = np.zeros(host + 256, np.uint8)
     assert B.spec_verify_attn(req, a, 1 << 20, dev, (staging.ctypes.data + 255) // 256 * 256, host, 0) == B.SPEC_ERR_HIP
+
+
+# ---- the LM head's tiles (sv_rules.h compiled by itself) ----------------------
+@pytest.fixture(scope="module")
+def geometry(tmp_path_factory):
+    import ctypes as C
+    import os
+    import subprocess
+    src = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_17074_amd", "csrc")
+    d = tmp_path_factory.mktemp("rules")
+    (d / "g.cpp").write_text('#include "sv_rules.h"\nextern "C" void geo(int M, int V, int K, int cus, int* o) {\n'
+                             '  const auto g = sv::lmh_geometry(M, V, K, cus);\n  o[0] = g.rb; o[1] = g.low_wr;'
+                             ' o[2] = g.tile_rows; o[3] = g.m_tiles; o[4] = g.nt;\n}\n')
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", src, str(d / "g.cpp"),
+                    "-o", str(d / "g.so")], check=True)
+    lib = C.CDLL(str(d / "g.so"))
+
+    def geo(M, V, K, cus=256):
+        o = (C.c_int * 5)()
+        lib.geo(M, V, K, cus, o)
+        return tuple(o)
+    return geo
+
+
+# rows, vocabulary, hidden width, low tiles; measured low / tall (weights from
+# HBM or, where a third of the cache holds them, from there)
+TILES = [
+    (20, 32000, 4096, True),      # 0.75
+    (72, 128256, 8192, True),     # 0.93 at 80 rows
+    (95, 50304, 1024, False),     # 57 / 42 us
+    (190, 50304, 4096, False),    # 147 / 126
+    (68, 111175, 5120, False),    # 280 / 247
+    (95, 128256, 2048, False),    # 161 / 142
+    (20, 50304, 4096, True),
+    (190, 78071, 4096, True),     # 0.96
+    (190, 32000, 8192, True),     # 0.89
+    (95, 32000, 1024, False),     # 39 / 33, cached
+    (95, 32000, 2048, True),      # 54 / 59
+    (125, 16000, 8192, True),     # 0.80
+    (125, 16000, 4096, False),    # 1.08, cached
+    (190, 16000, 4096, False),    # 85 / 80
+]
+
+
+@pytest.mark.parametrize("M,V,K,low", TILES)
+def test_lm_head_tiles(geometry, M, V, K, low):
+    assert (geometry(M, V, K)[1] > 0) == low
+
+
+def test_lm_head_tiles_cover_the_rows(geometry):
+    """Every shape gets a build that exists and tiles that hold its rows."""
+    rng = np.random.default_rng(3)
+    for _ in range(20000):
+        M, V, K = int(2 ** rng.uniform(0, 14)), int(2 ** rng.uniform(0, 20)), 32 * int(rng.integers(1, 512))
+        rb, wr, rows, mt, nt = geometry(M, V, K, int(rng.choice([1, 64, 256, 304])))
+        assert mt >= 1 and mt == -(-M // rows) and 4096 % nt == 0
+        if wr:
+            assert nt == 128 and mt == 1 and M <= 16 * rb * wr
+            assert (wr == 1 and 1 <= rb <= 6) or (wr == 2 and 4 <= rb <= 6)
+        else:
+            assert nt == 256 and 1 <= rb <= 6 and rows <= 64 * rb
