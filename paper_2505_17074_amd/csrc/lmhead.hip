@@ -327,17 +327,25 @@ struct TallGeo {
   static constexpr int RA = 16 * RB * WR;
   static constexpr int HST = RA * kRowB, WST = NT * kRowB;            // bytes of a slice of each matrix
   static constexpr int XH = RA / 8 / kWaves, XW = NT / 8 / kWaves;    // transfers per wave and slice
-  // slices in LDS: two of the hidden rows (L2 hits), and as many of the
-  // weights (from HBM) as fit, at most three
-  static constexpr int NW = 2 * HST + 3 * WST <= kLdsBytes ? 3 : 2;
-  static constexpr int LDS = 2 * HST + NW * WST;
+  // Slices in LDS: of the hidden rows (L2 hits) and of the weights (from HBM).
+  // 64- and 128-row tiles run where the vocabulary has few of them, so each
+  // compute unit's own latency shows: four and three of both, against two of
+  // the hidden rows and three of the weights 190 rows x 8192 x 16000 118.6 us for
+  // 134.2, 255 x 4096 x 1000 65.6 for 73.6 (weights from HBM; from the cache the
+  // same).  Taller ones have room for two of the hidden rows, and three of the
+  // weights up to 256 rows.
+  static constexpr int NH = RB == 1 ? 4 : RB == 2 ? 3 : 2;
+  static constexpr int NW = RB <= 2 ? NH : 2 * HST + 3 * WST <= kLdsBytes ? 3 : 2;
+  static constexpr int FLY = (NH - 2) * XH + (NW - 2) * XW;           // transfers behind the next slice's
+  static constexpr int LDS = NH * HST + NW * WST;
+  static_assert(NH == NW || (NH == 2 && NW == 3), "the next slice's transfers are older than the FLY youngest");
   // A slice's transfers are issued after the barrier that frees their stages,
   // or spread over the column blocks behind it.  Together they start sooner
   // but hold the waves' next products back: 192- and 384-row tiles measured
   // 109.6 and 181 us together, 112.7 and 187 spread (320 and 700 rows x 4096 x
   // 32000 with the acceptance), 256-row tiles 134.9 and 131.2 (480 rows).
   static constexpr bool SPREAD = RB == 4;
-  static_assert(RA % 64 == 0 && LDS <= kLdsBytes, "two slices in LDS");
+  static_assert(RA % 64 == 0 && LDS <= kLdsBytes, "the slices fit LDS");
 };
 
 template <int RB, bool BF16OUT>
@@ -376,7 +384,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     uint32_t step = 128u * (uint32_t)p.w_st;
     asm volatile("" : "+s"(step));
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        r, (lds_void_t*)(lds + 2 * G::HST + st * G::WST + w * 1024 + q * 8192), 16, woff + (q * step + kbytes(t)), 0, 0,
+        r, (lds_void_t*)(lds + G::NH * G::HST + st * G::WST + w * 1024 + q * 8192), 16, woff + (q * step + kbytes(t)), 0, 0,
         0);
   };
   // LDS addresses of this lane's operands, by k half, in the stage being read
@@ -386,7 +394,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   for (int h = 0; h < 2; ++h) {
     const uint32_t c = (uint32_t)(((4 * h + grp) ^ lmh_swz(l16)) * 16);
     aad[h] = (uint32_t)(16 * RB * wr + l16) * kRowB + c;
-    bad[h] = (uint32_t)(2 * G::HST) + (uint32_t)(16 * CB * wc + l16) * kRowB + c;
+    bad[h] = (uint32_t)(G::NH * G::HST) + (uint32_t)(16 * CB * wc + l16) * kRowB + c;
   }
 
   f32x4 acc[RB][CB];
@@ -398,14 +406,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   auto lda = [&](int h, int rb) { return *reinterpret_cast<const bf16x8*>(lds + aad[h] + rb * 16 * kRowB); };
   auto ldb = [&](int h, int cb) { return *reinterpret_cast<const bf16x8*>(lds + bad[h] + cb * 16 * kRowB); };
 #pragma unroll
-  for (int q = 0; q < G::XW; ++q) xfer_w(0, 0, q);
+  for (int st = 0; st < G::NW - 1; ++st) {
 #pragma unroll
-  for (int q = 0; q < G::XH; ++q) xfer_h(0, 0, q);
-  if constexpr (G::NW == 3)
+    for (int q = 0; q < G::XW; ++q) xfer_w(st, st, q);
+    if (st < G::NH - 1)
 #pragma unroll
-    for (int q = 0; q < G::XW; ++q) xfer_w(1, 1, q);
+      for (int q = 0; q < G::XH; ++q) xfer_h(st, st, q);
+  }
   lmh_setup(p);                     // its host reads fly beside the first slices
-  lmh_wait_vm<(G::NW - 2) * G::XW>();
+  lmh_wait_vm<G::FLY>();
   lmh_barrier();
   b[0] = ldb(0, 0);
 #pragma unroll
@@ -415,14 +424,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // the last column block each hidden operand is replaced by the next half's
   // as its last product is issued (past the last slice: by what the ring
   // holds, never used).
-  int hstep = G::HST, wstage = 0;   // to the other stage of the hidden rows; the weights' stage
+  int hstage = 0, wstage = 0;       // the current slice's stages
   // During slice s (or, together, from the barrier that ends slice s - 1):
-  // transfers h0 .. h1 of the hidden rows' slice s + 1 and w0 .. w1 of the
+  // transfers h0 .. h1 of the hidden rows' slice s + NH - 1 and w0 .. w1 of the
   // weights' slice s + NW - 1, into the stages that slice s - 1 left.
   auto ahead = [&](int s, int h0, int h1, int w0, int w1) {
-    const int hs = (s + 1) & 1, ws = wstage == 0 ? G::NW - 1 : wstage - 1;
+    const int hs = hstage == 0 ? G::NH - 1 : hstage - 1, ws = wstage == 0 ? G::NW - 1 : wstage - 1;
 #pragma unroll
-    for (int q = h0; q < h1; ++q) xfer_h(hs, s + 1, q);
+    for (int q = h0; q < h1; ++q) xfer_h(hs, s + G::NH - 1, q);
 #pragma unroll
     for (int q = w0; q < w1; ++q) xfer_w(ws, s + G::NW - 1, q);
   };
@@ -433,18 +442,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int cb = 0; cb < CB; ++cb) {
       if (H == 1 && cb + 1 == CB) {
         // Every operand of this slice has been read: the next slice has landed
-        // (the weights of the one after may still fly), everyone is done
-        // with this one, and later slices may overwrite it.
-        lmh_wait_vm<(G::NW - 2) * G::XW>();
+        // (those after it may still fly), everyone is done with this one, and
+        // later slices may overwrite it.
+        lmh_wait_vm<G::FLY>();
         lmh_barrier();
+        const int hstep = hstage + 1 == G::NH ? -(G::NH - 1) * G::HST : G::HST;
         const int wstep = wstage + 1 == G::NW ? -(G::NW - 1) * G::WST : G::WST;
+        hstage = hstage + 1 == G::NH ? 0 : hstage + 1;
         wstage = wstage + 1 == G::NW ? 0 : wstage + 1;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           aad[h] += hstep;
           bad[h] += wstep;
         }
-        hstep = -hstep;
         if constexpr (!G::SPREAD) ahead(t + 1, 0, G::XH, 0, G::XW);
       } else if constexpr (G::SPREAD) {
         if (H == 0 && cb < G::XH) ahead(t, cb, cb + 1, 0, 0);

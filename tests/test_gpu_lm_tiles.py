@@ -1,8 +1,8 @@
 """The LM head's tile shapes at their edges: rows around each tile height (the
 low tiles' 16-row blocks, 96 / 97 and 192 / 193 rows, 64-row steps of the tall
-tiles, several row tiles), vocabularies around the 128- and 256-entry tiles,
-hidden widths of a partial, one, two and three slices and one that starts
-rotated, padded row strides, fp32 and bf16 logits.  Logits against fp64 within
+tiles, several row tiles; every build, which test_plan_rules.py checks),
+vocabularies around the 128- and 256-entry tiles, hidden widths of a partial,
+one, two and three slices and of more than the rings hold, rotated starts, padded row strides, fp32 and bf16 logits.  Logits against fp64 within
 the bound of fp32 accumulation of exact bf16 products (K 2^-23 sum |h w|, plus
 half a bf16 ulp, 2^-8 |x|, where stored in bf16); tokens against spec_accept on
 the stored logits (the sampled values are fixed by the seed, away from ties)."""
@@ -20,6 +20,13 @@ CASES = [  # rows, vocabulary, hidden width, bf16 logits
     (97, 32900, 96, True), (128, 33001, 192, False), (161, 32800, 320, False), (192, 32769, 32, True),
     (193, 1000, 64, False), (256, 257, 192, True), (257, 5000, 96, False), (320, 32900, 128, False),
     (385, 32000, 64, True), (449, 32000, 32, False), (716, 32100, 320, False), (960, 32000, 96, True),
+    # low tiles of 65 to 192 rows (weights too long for the cache), 21 and 21.5 slices
+    (66, 32700, 1344, False), (80, 32700, 1344, True), (96, 32640, 1376, False), (97, 32700, 1344, True),
+    (130, 32700, 1344, False), (161, 32700, 1376, True), (192, 32640, 1344, False),
+    # tall tiles of 64, 128 and 192 rows over more slices than their rings hold
+    # (7 and 8, also 6.5 and 7.5; 5 would start every tile at slice 0)
+    (100, 1000, 512, False), (70, 5000, 480, True), (193, 32000, 448, False), (256, 32000, 416, True),
+    (240, 32000, 448, True), (257, 32000, 416, False), (320, 32000, 448, True), (384, 32000, 448, False),
 ]
 
 

@@ -229,3 +229,13 @@ def test_lm_head_tiles_cover_the_rows(geometry):
             assert (wr == 1 and 1 <= rb <= 6) or (wr == 2 and 4 <= rb <= 6)
         else:
             assert nt == 256 and 1 <= rb <= 6 and rows <= 64 * rb
+
+
+def test_lm_tile_cases_launch_every_build(geometry):
+    """The GPU test's cases select every build of both kernels, and each tall
+    one over more slices than its ring holds as well."""
+    import test_gpu_lm_tiles as T
+    got = {(g[1], g[0]) for g in (geometry(M, V, K) for M, V, K, _ in T.CASES)}
+    assert got == {(1, rb) for rb in range(1, 7)} | {(2, rb) for rb in range(4, 7)} | {(0, rb) for rb in range(1, 7)}
+    long = {g[0] for g in (geometry(M, V, K) for M, V, K, _ in T.CASES if K > 4 * 64) if g[1] == 0}
+    assert {1, 2, 3} <= long
