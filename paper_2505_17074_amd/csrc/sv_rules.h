@@ -225,18 +225,19 @@ struct LmhGeometry {
 // Measured as low over tall tiles' time, weights from HBM (the cache between
 // the calls full of other reads):
 //  - up to one round of low tiles: tall ones leave half the compute units
-//    without any.  V = 32000, K = 1024 to 8192: M = 20 0.84-0.73, 95 0.97-0.77,
-//    190 1.02-0.89; V = 9000, M = 20 0.78-0.52, 125 0.98-0.80, 160 1.07-0.92.
+//    without any.  V = 32000, K = 1024 to 8192: M = 20 0.89-0.82, 95 1.01-0.85,
+//    190 1.02-0.94; V = 9000, M = 20 0.83-0.62, 125 1.01-0.92, 160 1.12-1.07.
 //    Weights that stay in the Infinity Cache between calls (256 MB) favour the
 //    tall tiles' cached loads beyond 64 rows: V = 32000, K = 1024, M = 95 1.07, V
 //    = 16000, K = 4096, M = 125 1.08, 160 1.20;
 //  - more rounds, fewer than two for each of the tall tiles': V = 78071, M =
-//    20 0.85-0.79, 95 0.99-0.86, 190 0.99-0.96;
+//    20 0.87-0.84, 95 1.01-0.89, 190 1.07-1.02 (from the cache, K = 2048 on, 95
+//    0.95-0.85, 190 0.98);
 //  - two for each: their epilogues, and a last round that is partly empty, are
-//    paid twice.  V = 50304, M = 20 1.02-0.98, 40 1.08, 95 1.15, 190 1.27.
+//    paid twice.  V = 50304, M = 20 1.00-0.98, 40 1.07, 95 1.18, 190 1.28.
 //    Where every round is full and the weights are long they pay later: V =
-//    128256, K = 4096, M = 40 0.99, 60 1.05, 95 1.08; K = 8192, M = 60 0.99,
-//    80 0.93, 95 0.97.
+//    128256, K = 4096, M = 40 0.97, 60 1.02, 95 1.08; K = 8192, M = 60 0.95,
+//    95 0.94.
 inline bool lmh_low_tiles(int M, int V, int K, int cus) {
   const int64_t tiles = ((int64_t)V + kLmhNTLow - 1) / kLmhNTLow;
   const int64_t rounds = (tiles + cus - 1) / cus;
