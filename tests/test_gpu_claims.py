@@ -92,7 +92,9 @@ def test_claims_repeated_calls_and_full_step(gpu_lib, claims):
     previous call's value) give the static launch's outputs every time, the
     acceptance's included."""
     name = "claims_repeat"
-    pool = U.custom_pool(ctx=[7000, 150, 16000, 900], k=[8, 3, 8, 5], Hq=32, Hkv=8, seed=U.case_seed(name))
+    pool = U.custom_pool(ctx=[7000, 150, 40000, 900], k=[8, 3, 8, 5], Hq=32, Hkv=8, seed=U.case_seed(name))
+    # enough K/V for two streams (the rule's line: 165 MiB with the logits)
+    assert 2 * (int(pool.ctx_len.sum()) + int(pool.n_q.sum())) * 8 * 128 * 2 > 170 << 20
     print(f"[case] {name} static", flush=True)
     claims(STATIC, "0")
     ref = _attention(pool, 384, which="verify")

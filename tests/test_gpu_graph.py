@@ -46,7 +46,10 @@ def test_graph_replays_match_eager_calls(gpu_lib, monkeypatch, entry):
     name = "graph_" + entry
     seed = U.case_seed(name)
     print(f"[case] {name} seed {seed}", flush=True)
-    pool = U.custom_pool(ctx=[7000, 150, 16000, 900], k=[8, 3, 8, 5], Hq=32, Hkv=8, seed=seed)
+    pool = U.custom_pool(ctx=[7000, 150, 40000, 900], k=[8, 3, 8, 5], Hq=32, Hkv=8, seed=seed)
+    # spec_verify forks onto its side stream (over 165 MiB of K/V and logits),
+    # so its captured graph holds the fork and the join
+    assert 2 * (int(pool.ctx_len.sum()) + int(pool.n_q.sum())) * 8 * 128 * 2 > 170 << 20
     b = DeviceBatch(pool, "cuda")
     req, attn, acc = b.requests(), b.attn_args(384), b.accept_args()
     st, dev_bytes, host_bytes = B.spec_workspace_bytes(req, attn, acc)

@@ -89,16 +89,19 @@ def test_step_on_one_or_two_streams(gpu_lib, name, n, ctx, k, V, two):
 
 
 @pytest.mark.gpu
-def test_workspace_kept_from_another_batch(gpu_lib):
-    """A workspace and a staging buffer that hold four pieces per stream, not
-    the 24 that the automatic split cuts: longer pieces run in them,
-    and nothing is written past their ends."""
-    print("[small] kept workspace", flush=True)
-    pool = U.custom_pool(ctx=[3000], k=[4], Hq=32, Hkv=8, seed=9)
+@pytest.mark.parametrize("qkv", [W.BF16, W.F32], ids=["bf16", "f32"])
+def test_workspace_kept_from_another_batch(gpu_lib, qkv):
+    """A workspace and a staging buffer that hold four pieces per stream (fp32: six;
+    the longer pieces are of half the rows an item), not those the automatic
+    split cuts: longer ones run in them, and nothing is written past their
+    ends."""
+    print(f"[small] kept workspace {qkv}", flush=True)
+    f32 = qkv == W.F32
+    pool = U.custom_pool(ctx=[3000], k=[4] if not f32 else [15], Hq=32, Hkv=8, seed=9, qkv=qkv)
     b = DeviceBatch(pool, "cuda")
-    ref, bound = reference_and_bound(pool, P_REL)
+    ref, bound = reference_and_bound(pool, 0.0 if f32 else P_REL)
     a = b.attn_args()
-    a.split_kv = 768
+    a.split_kv = 768 if not f32 else 512
     req = b.requests()
     st, dev, host = B.spec_workspace_bytes(req, a, None)
     B.check(st, "workspace of four pieces")
@@ -115,6 +118,70 @@ def test_workspace_kept_from_another_batch(gpu_lib):
     torch.cuda.synchronize()
     assert (np.abs(b.out.cpu().numpy() - ref) <= bound).all()
     assert bool((ws[dev:] == 0xA5).all()) and bool((staging[host:] == 0xA5).all())
+
+
+@pytest.mark.gpu
+def test_noalloc_runs_the_longer_pieces(gpu_lib):
+    """A step whose automatic split does not fit the static scratch beside the
+    acceptance's statistics of a 4M-entry vocabulary, and whose longer pieces
+    do: attention against fp64 for some of the requests, the acceptance as
+    spec_accept gives it."""
+    print("[small] noalloc, longer pieces", flush=True)
+    n, k, ctx, V, d, Hq = 100, 9, 12000, 4000000, 128, 8
+    nq = n * (k + 1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16)
+    q, kk, vv = normal(nq, Hq, d), normal(n * (ctx + k + 1), 1, d), normal(n * (ctx + k + 1), 1, d)
+    out = torch.full((nq, Hq, d), float("nan"), device="cuda")
+    logits, probs = normal(nq, V), torch.empty((n * k, V), dtype=torch.bfloat16, device="cuda")
+    for r in range(0, n * k, 50):
+        probs[r:r + 50] = torch.softmax(2 * normal(min(50, n * k - r), V).float(), -1).bfloat16()
+    tokens = torch.randint(0, V, (n * k,), generator=g, device="cuda", dtype=torch.int32)
+    uniforms = torch.rand(nq, generator=g, device="cuda") * 0.5
+    req = B.make_requests(np.full(n, ctx), np.full(n, k))
+    a = B.SpecAttnArgs()
+    a.num_q_heads, a.num_kv_heads, a.head_dim, a.dtype = Hq, 1, d, B.SPEC_BF16
+    a.q, a.k, a.v, a.out = q.data_ptr(), kk.data_ptr(), vv.data_ptr(), out.data_ptr()
+    a.q_stride_tok, a.q_stride_head, a.kv_stride_tok, a.kv_stride_head = Hq * d, d, d, d
+    acc = []
+    for _ in range(2):
+        o = [torch.full((n,), -5, dtype=torch.int32, device="cuda") for _ in range(3)]
+        c = B.SpecAcceptArgs()
+        c.vocab, c.dtype, c.logits_stride, c.probs_stride = V, B.SPEC_BF16, V, V
+        c.target_logits, c.draft_probs = logits.data_ptr(), probs.data_ptr()
+        c.draft_tokens, c.uniforms = tokens.data_ptr(), uniforms.data_ptr()
+        c.accepted_len, c.next_token, c.accepted_node = (x.data_ptr() for x in o)
+        acc.append((c, o))
+    st, dev, _ = B.spec_workspace_bytes(req, a, acc[0][0])
+    assert st == B.SPEC_OK and dev > B.SPEC_NOALLOC_SCRATCH_BYTES
+    h = torch.cuda.current_stream().cuda_stream
+    B.check(B.spec_verify_noalloc(req, a, acc[0][0], h), "spec_verify_noalloc")
+    st, dev, host = B.spec_workspace_bytes(req, None, acc[1][0])
+    B.check(st, "workspace")
+    ws = torch.empty(dev + 256, dtype=torch.uint8, device="cuda")
+    staging = torch.empty(host, dtype=torch.uint8, pin_memory=True)
+    B.check(B.spec_accept(req, acc[1][0], (ws.data_ptr() + 255) // 256 * 256, dev, staging.data_ptr(), host, h), "accept")
+    torch.cuda.synchronize()
+    for x, y in zip(acc[0][1], acc[1][1]):
+        assert torch.equal(x, y)
+    assert int(acc[0][1][1].min()) >= 0
+    L = ctx + k + 1
+    see = torch.ones((k + 1, L), dtype=torch.bool, device="cuda")
+    see[:, ctx:] = torch.tril(see[:, ctx:])
+    for i in (0, 1, 57, n - 1):
+        K, V_ = kk[i * L:(i + 1) * L, 0].double(), vv[i * L:(i + 1) * L, 0].double()
+        for hh in range(Hq):
+            qq = q[i * (k + 1):(i + 1) * (k + 1), hh].double()
+            s = (qq @ K.t().contiguous()) / d ** 0.5
+            p = torch.softmax(s.masked_fill(~see, -float("inf")), -1)
+            # scores off by (d + 4) 2^-24 sum|q k| / sqrt(d), as test_gpu_f32_attn.py derives
+            ds = (qq.abs() @ K.abs().t().contiguous() / d ** 0.5).max(-1).values * (d + 4) * 2.0 ** -24
+            bound = (2 * ds[:, None] + (L + 16) * 2.0 ** -24 + P_REL) * (p @ V_.abs())
+            got = out[i * (k + 1):(i + 1) * (k + 1), hh].double()
+            assert bool(((got - p @ V_).abs() <= bound).all()), (i, hh)
 
 
 @pytest.mark.skipif(torch.cuda.is_available(), reason="made-up device pointers: only where nothing can be launched")
