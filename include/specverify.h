@@ -66,15 +66,24 @@
  *     (surplus work-groups >= 0) override the first round and the surplus;
  *     they exist for tests.
  *   - When the verify attention cuts a request's KV range into pieces, a
- *     separate combine kernel follows, or, in batches of more streams than
- *     half a round of work-groups and with a caller's split_kv (bf16 inputs,
- *     partial blocks up to 64 KB per stream), the last piece of each (request, KV head, head
- *     group) to finish combines the pieces' partial outputs.  The environment
- *     variable SPEC_FUSED_COMBINE_MAX_BYTES (a byte count) replaces that
- *     choice's limit; the outputs agree either way within the attention
- *     tolerance, and each choice is deterministic.
+ *     separate combine kernel follows, or the last piece of each (request,
+ *     KV head, head group) to finish combines the pieces' partial outputs.
+ *     The latter takes bf16 inputs and partial blocks of up to 64 KB per
+ *     stream, and runs with a caller's split_kv, or with at least half as
+ *     many streams as the device runs work-groups at once (three eighths
+ *     where no stream has more than two pieces or the blocks are at most
+ *     6 KB).  The environment variable SPEC_FUSED_COMBINE_MAX_BYTES (a byte
+ *     count) replaces that choice's limit; the outputs agree either way
+ *     within the attention tolerance, and each choice is deterministic.
  *   - Results are deterministic: the same inputs give bit-identical outputs
- *     (fixed reduction orders, no floating-point atomics).
+ *     (fixed reduction orders, no floating-point atomics), in scratch of at
+ *     least the sizes that spec_workspace_bytes() gives for them.  In less
+ *     (or in spec_verify_noalloc's static scratch, when it is too small for
+ *     the automatic split) the longer pieces sum in another order: the
+ *     outputs of two such calls are bit-identical, and agree with the
+ *     automatic split's within the attention tolerance.
+ *   - A bf16 probability is carried as the sum of two bf16 parts, the second
+ *     of either sign: an infinity in V gives an infinity or a NaN.
  *   - A call captured into a HIP graph may be replayed any number of times,
  *     also with other calls on the same workspace in between: the tagged
  *     words are left by each call ready for its own tag again.  A replay
@@ -169,8 +178,8 @@ typedef struct spec_requests {
  *   1/sqrt(d).  dtype SPEC_BF16 (MFMA path) or SPEC_F32; d in {64, 128}.
  *   split_kv 0 = automatic split of long contexts; otherwise the number of
  *   KV positions per split (a positive multiple of 32) -- results agree
- *   across splits within fp32 rounding.  Requests split more than once are
- *   merged by a second (combine) kernel.
+ *   across splits within fp32 rounding.  The pieces of a request are merged
+ *   by a second (combine) kernel or by the last of them (above).
  *
  * Paged KV cache (block_table != NULL; the PagedAttention layout the paper
  * cites as serving practice, Sec. 6.2): k and v are page pools
@@ -310,7 +319,9 @@ typedef struct spec_lm_head_args {
 } spec_lm_head_args_t;
 
 /* Workspace sizes for a call with these arguments (either args pointer may
- * be NULL when that part is not run).  The device workspace must be
+ * be NULL when that part is not run): the larger of what the automatic split
+ * and the one of longer pieces need, so scratch sized for one batch serves
+ * every batch whose sizes are no larger.  The device workspace must be
  * 256-byte aligned; the host staging buffer should be pinned
  * (hipHostMalloc), so that the kernels read the plan where it was staged. */
 SPEC_API spec_status_t spec_workspace_bytes(const spec_requests_t* req,
