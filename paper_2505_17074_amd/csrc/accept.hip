@@ -430,10 +430,10 @@ __device__ __forceinline__ double load_dev(const double* p) {
 //   fp64 scan inside it (for p, in that chunk's units exp(l - m_c)), the
 //   smallest token id whose cumulative weight exceeds the target.
 // TILES: the statistics are the LM head's per-tile ones (p.tiles), folded
-// here; otherwise the row-statistics kernel's chunk statistics.  A separate
-// build, so the verify path keeps the smaller register footprint (80 VGPRs
-// against 96 with the tile fold's held loads: 6 waves per SIMD instead of 5
-// beside the attention).
+// here; otherwise the row-statistics kernel's chunk statistics.  Separate
+// builds, so that the verify path keeps the smaller register footprint (75 VGPRs,
+// 6 waves per SIMD beside the attention; with 4, 8 and 16 held loads of the tile
+// fold 75, 88 and 130: 6, 5 and 3 waves, with no attention beside them).
 template <typename T, int HELD>
 __global__ __launch_bounds__(kAccThreads) void acc_decide_select(AccParams p) {
   constexpr bool TILES = HELD > 0;
@@ -873,7 +873,7 @@ __device__ __forceinline__ bool seq_exchange(const AccParams& p, int i, int c, i
   // The pairs on C lanes of the wave that polled, after its poll: one round
   // trip (one thread reading them in turn took C).  With the rows folded on 16
   // lanes and the block sums on the vector ALU, 64 15-node trees over 32000
-  // fp32 logits on four work-groups each: 62.4 -> 56.8 us with the row pass.
+  // fp32 logits on four work-groups each: 61.4 -> 57.2 us with the row pass.
   asm volatile("" ::: "memory");
   __builtin_amdgcn_wave_barrier();
   if (threadIdx.x < C) {

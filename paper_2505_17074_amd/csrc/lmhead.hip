@@ -1,8 +1,9 @@
 // The target model's LM head for the verify step (gfx950): the verify
 // positions' logits, logits = hidden . weight^T, the forward that produces
 // the target distributions of Eq. (1) (Sec. 2.2), with the softmax
-// statistics of every (row, 256-entry tile) taken in the epilogue so that
-// the acceptance never re-reads the logits for its normalisers.
+// statistics of every (row, vocabulary tile) taken in the epilogue so that the
+// acceptance never re-reads the logits for its normalisers (tiles of 128
+// entries under lmh_low, 256 under lmh_tall).
 //
 // hidden [M, K] and weight [V, K] (one row per vocabulary entry, the linear
 // layer's layout) are bf16 and both contiguous along K, so the operands of
@@ -13,25 +14,30 @@
 // 64-k slices of the hidden rows and the weight rows (one 128-byte cache line
 // per row) stream through LDS by direct buffer -> LDS transfers; the 16-byte
 // chunks of a row are swizzled so that the operand reads hit every bank.  Eight
-// waves, one work-group per CU.  Two kernels by M:
+// waves, one work-group per CU.  Two kernels, chosen by rows, rounds of
+// work-groups and weight size (lmh_low_tiles):
 //
-//  - lmh_low (M <= 192): every row against 128 vocabulary entries, a deep ring
-//    whose stream runs on from tile to tile.  Bound by the weights' stream:
-//    20 x 4096 x 32000 (262 MB) 41 us of GEMM, 72 x 8192 x 128256 (2.1 GB) 342
-//    us, 6.2-6.4 TB/s.  What it took over 256-entry tiles of 64 or 128 rows
-//    (59 and 395 us): all CUs busy on one vocabulary, the transfers' offsets
-//    out of the scalar unit (descriptors rebuilt per transfer held the ring at
-//    4.8 TB/s), each tile starting at another k slice (rows a power of two
-//    apart otherwise queue on the same channels: 425 -> 378 us), and the
-//    epilogue's reductions on the vector ALU (12 -> 5 us a tile).
+//  - lmh_low (up to 192 rows): every row against 128 vocabulary entries, a deep
+//    ring whose stream runs on from tile to tile.  Bound by the weights' stream
+//    up to about 80 rows: 20 x 4096 x 32000 (262 MB) 41 us of GEMM, 72 x 8192 x
+//    128256 (2.1 GB) 342 us, 6.2-6.4 TB/s.  With more rows every CU's own reads
+//    of all of them (from L2, one 64-k slice per slice of weights) weigh in: 160
+//    x 4096 x 32000 67.7 us for 262 MB of weights and 21 of logits, 4.2 TB/s,
+//    with 256 CUs x 1.3 MB of hidden rows beside them.  What it took over
+//    256-entry tiles of 64 or 128 rows (59 and 395 us at 20 and 72 rows): all
+//    CUs busy on one vocabulary, the transfers' offsets out of the scalar unit
+//    (descriptors rebuilt per transfer held the ring at 4.8 TB/s), each tile
+//    starting at another k slice (lmh_first_slice), and the epilogue's
+//    reductions on the vector ALU (12 -> 5 us a tile).
 //  - lmh_tall: 64 RB rows x 256 entries (RB <= 6), 4 x 2 waves of 16 RB x 128.
-//    Bound by the matrix cores and by what a slice's hand-over leaves idle.  A
-//    wave keeps its RB hidden operands in registers over a half slice and
-//    passes the weight operands through two, so 384 x 256 fits 256 registers
-//    and 700 rows take one round of work-groups: 716 x 4096 x 32000 160 us
-//    (1.17 PFLOP/s; the products alone, without transfers, 120) against 202
-//    for two rounds of 192-row tiles whose operands were read a slice at a
-//    time; 92 MB of logits take 15 us of the epilogue.
+//    Bound by the matrix cores and by what a slice's hand-over leaves idle, and
+//    by the weights' latency where the vocabulary is short.  A wave keeps its
+//    RB hidden operands in registers over a half slice and passes the weight
+//    operands through two, so 384 x 256 fits 256 registers and 700 rows take
+//    one round of work-groups: 716 x 4096 x 32000 with the acceptance 188 us,
+//    against 223 for two rounds of 192-row tiles whose operands were read a
+//    slice at a time (the products alone, without transfers, 120 of the GEMM);
+//    92 MB of logits take 15 us of the epilogue.
 #include "sv_internal.h"
 
 #include <algorithm>
@@ -43,6 +49,12 @@ namespace {
 #ifndef SV_LMH_LOW_NS
 #define SV_LMH_LOW_NS 8
 #endif
+// Cache policy of the low tiles' weight transfers: non-temporal (2) keeps the
+// weights, read once a call, from displacing the hidden rows and each other.
+// GEMM and acceptance, us non-temporal / default, calls in a row: 20 rows x 4096
+// x 32000 56.1 / 58.2, 80 x 8192 x 32000 101 / 117, 70 x 8192 x 128256 385 / 410;
+// weights that stay in the Infinity Cache lose to it by less: 20 x 4096 x 9000
+// 40.7 / 39.0 (46.0 / 46.7 when they come from HBM).
 #ifndef SV_LMH_W_CPOL
 #define SV_LMH_W_CPOL 2
 #endif
@@ -98,6 +110,14 @@ __device__ __forceinline__ LmhTile lmh_tile(const LmhParams& p, int item) {
   return t;
 }
 
+// Each vocabulary tile starts its walk over K at another slice, 5 slices on
+// from its neighbour's (K of whole slices only): rows a power of two apart
+// read in step queue on the same memory channels.  GEMM and acceptance, us with
+// steps of 0 / 1 / 3 / 5 slices: low tiles 20 x 4096 x 32000 71.2 / 54.9 / 56.2 /
+// 56.1, 80 x 8192 x 32000 131.6 / 101.1 / 100.9 / 101.2, 70 x 8192 x 128256 477 /
+// 383 / 381 / 385; tall 64 x 4096 x 50304 103.6 / 97.7 / 95.9 / 95.2, 380 179.7 /
+// 175.7 / 186.5 / 183.2, 700 x 4096 x 32000 191 / 195 / 199 / 197.  Any step
+// does for the low tiles; 5 shares no factor with 16, 32, 64 and 128 slices.
 #ifndef SV_LMH_STAG
 #define SV_LMH_STAG 5
 #endif
@@ -240,7 +260,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // The ring runs on over this work-group's tiles (blockIdx.x, + gridDim.x,
   // ...): the next tile's first slices are in flight during a tile's last
   // ones and its epilogue.  Past the last tile the weights' descriptor is
-  // empty (zeros, no traffic).
+  // empty (zeros, no traffic); the hidden rows' transfers go on, up to NS - 1
+  // slices of L2 hits that nothing reads, so that the counts stay the same.
   int ilt = blockIdx.x, it = 0, iks = lmh_first_slice(p, ilt, nk);   // tile, slice count and k slice to issue
   auto wrows = [&](int nt) {
     return lmh_rows(p.weight + (int64_t)nt * G::NT * p.w_st, min(G::NT, p.V - nt * G::NT), p.w_st, p.K);
@@ -341,9 +362,11 @@ struct TallGeo {
   static_assert(NH == NW || (NH == 2 && NW == 3), "the next slice's transfers are older than the FLY youngest");
   // A slice's transfers are issued after the barrier that frees their stages,
   // or spread over the column blocks behind it.  Together they start sooner
-  // but hold the waves' next products back: 192- and 384-row tiles measured
-  // 109.6 and 181 us together, 112.7 and 187 spread (320 and 700 rows x 4096 x
-  // 32000 with the acceptance), 256-row tiles 134.9 and 131.2 (480 rows).
+  // but hold the waves' next products back.  GEMM and acceptance, us together /
+  // spread, one round of RB = 1 .. 6 (64, 128, 190, 255, 320 and 380 rows x 4096 x
+  // 50304): 95.2 / 95.2, 109.2 / 110.5, 125.5 / 127.2, 137.8 / 141.0, 157 / 176,
+  // 183 / 193; RB = 4 over two rounds (480 x 4096 x 32000) 141.0 / 138.4 and four
+  // (960 rows) 278.6 / 277.0.
   static constexpr bool SPREAD = RB == 4;
   static_assert(RA % 64 == 0 && LDS <= kLdsBytes, "the slices fit LDS");
 };

@@ -71,9 +71,10 @@ inline bool fuse_by_default(int64_t streams, int64_t slots, int64_t nseg_max, in
 
 // The estimates below were fitted to 1398 calls of uniform batches (8 to 256
 // streams of 130 to 64000 keys, 5 to 72 rows, d = 64 and 128, bf16 and fp32,
-// whole and in 2 to 512 pieces): 4 % RMS of the call's time, and the plan of
-// least estimate is 0.4 % slower than the best one measured on average, 11 %
-// at worst (8 streams of 300 keys, d = 64: 13.5 against 12.2 us).
+// whole and in 2 to 512 pieces): 8 % RMS of the call's time beside a constant
+// 9.5 us, and the plan of least estimate is 0.4 % slower than the best one
+// measured on average, 14 % at worst (8 streams of 400 keys, 5 rows, d = 128:
+// 18.2 against 16.0 us).
 
 // Microseconds of one round of work-groups: its longest piece at a
 // work-group's own rate, or the batch's K and V at the HBM rate; where the two

@@ -354,7 +354,7 @@ def test_per_request_trees_size_like_the_shared_tree(lib):
 def test_claim_word_in_the_workspace(lib, monkeypatch):
     """When the bf16 split kernel has more items than its first round of
     work-groups, the later work-groups claim items from one word in the
-    workspace (one more 256-byte section); the fp32 VALU kernel never claims,
+    workspace (one more 256-byte section); the fp32 kernel never claims,
     and malformed environment values are ignored."""
     req = _req(ctx=(3000, 5000))
     monkeypatch.setenv("SPEC_ATTN_FIRST_ROUND", str(1 << 20))
@@ -379,7 +379,7 @@ def test_fused_combine_counters_in_the_workspace(lib, monkeypatch):
     """Split streams whose partial blocks are under the planner's limit are
     combined inside the bf16 split kernel, which needs one arrival counter per
     split stream in the workspace; the environment limit turns that off, and
-    fp32 inputs (the VALU kernel) never use it."""
+    fp32 inputs never use it."""
     req = _req(ctx=(3000, 5000))
     fused = _ws(req, _attn(split_kv=1024), None)           # 16 rows x 5 pieces x 512 B = 40 KB
     monkeypatch.setenv("SPEC_FUSED_COMBINE_MAX_BYTES", "0")

@@ -65,13 +65,13 @@ def _check_accept(pool, lmv, got_logits, tag, rule=B.SPEC_TREE_INDEPENDENT):
 CASES = [
     # (config, batch, hidden_dim, vocab override)
     ("tiny_f32", 4, 256, None),          # fp32 logits, 1024 entries
-    ("mha7b_b32", 3, 64, 1000),          # vocabulary not a multiple of the 256-entry tile
+    ("mha7b_b32", 3, 64, 1000),          # vocabulary not a multiple of a tile
     ("long_gqa_b8", 1, 128, 4099),       # bf16 logits, ragged vocabulary
-    ("ragged_gqa_b128", 24, 256, 5000),  # 2 row tiles
+    ("ragged_gqa_b128", 24, 256, 5000),  # 131 rows: three row tiles
     ("tree15_b64", 3, 512, 3000),        # token tree, every row's statistics from the GEMM
-    ("mha7b_b32", 32, 4096, None),       # LLaMA-7B LM head at the full workload (160 rows)
-    ("ragged_gqa_b128", 128, 4096, None),  # full workload: 716 rows, 192-row tiles
-    ("tree15_b64", 64, 4096, None),      # full workload: 960 rows, 256-row tiles
+    ("mha7b_b32", 32, 4096, None),       # LLaMA-7B LM head at the full workload (160 rows, low tiles)
+    ("ragged_gqa_b128", 128, 4096, None),  # full workload: 716 rows, two 358-row tiles
+    ("tree15_b64", 64, 4096, None),      # full workload: 960 rows, four 240-row tiles
     ("tiny_f32", 5, 96, 700),            # hidden width 96: a 64-k slice, then a 32-k tail slice
     ("mha7b_b32", 2, 32, 513),           # hidden width 32: the tail slice alone
 ]

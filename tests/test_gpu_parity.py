@@ -194,6 +194,7 @@ def test_deterministic(gpu_lib):
 EDGE = [
     ("ctx_edges_k0_k16", dict(ctx=[0, 1, 31, 32, 33, 100], k=[0, 1, 16, 4, 0, 7])),
     ("d64_mha", dict(ctx=[17, 300, 64], k=[3, 0, 8], Hq=4, Hkv=4, d=64)),
+    # (the names fix the seeds; fp32 attention runs on the fp32 matrix cores)
     ("f32_valu_gqa_d128", dict(ctx=[5, 130, 70], k=[2, 6, 0], Hq=8, Hkv=2, d=128, qkv=W.F32)),
     ("f32_valu_d64", dict(ctx=[200, 0], k=[16, 3], Hq=2, Hkv=1, d=64, qkv=W.F32)),
     ("tree_nonbinary", dict(ctx=[0, 50, 300], tree_parent=[-1, 0, 0, 0, 1, 1, 2, 4, 4, 7])),
