@@ -72,14 +72,14 @@ def test_attention_of_an_infinite_value(gpu_lib, dtype, d, split):
 
 
 @pytest.mark.parametrize("logit", [W.F32, W.BF16])
-@pytest.mark.parametrize("rule", ["independent", "sequential"])
-@pytest.mark.parametrize("V,kw", [(20000, dict(k=[4, 0, 8])), (20000, dict(tree_parent=[-1, 0, 0, 1, 1, 2])),
-                                  (140000, dict(tree_parent=[-1, 0, 0, 0]))], ids=["chain", "tree", "tree35chunks"])
+@pytest.mark.parametrize("V,kw,rule", [
+    (20000, dict(k=[4, 0, 8]), "independent"), (20000, dict(tree_parent=[-1, 0, 0, 1, 1, 2]), "independent"),
+    (20000, dict(tree_parent=[-1, 0, 0, 1, 1, 2]), "sequential"), (140000, dict(tree_parent=[-1, 0, 0, 0]), "independent"),
+    (140000, dict(tree_parent=[-1, 0, 0, 0]), "sequential"),
+], ids=["chain", "tree", "tree_seq", "tree35chunks", "tree35chunks_seq"])
 def test_acceptance_with_lowest_value_masks(gpu_lib, V, kw, rule, logit):
     """The first two chunks of 4096 entries, and the last ones, masked by the
     logit type's lowest finite value, in every row."""
-    if rule == "sequential" and "k" in kw:
-        pytest.skip("a chain has one rule")
     print(f"[extreme] accept V {V} {logit} {rule} {kw}", flush=True)
     pool = U.custom_pool(ctx=[1] * 3, Hq=1, Hkv=1, d=64, V=V, logit=logit, sigma=0.5, seed=7, **kw)
     lowest = np.float32(np.finfo(np.float32).min) if logit == W.F32 else np.uint16(0xFF7F)
