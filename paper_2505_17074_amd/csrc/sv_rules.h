@@ -211,6 +211,13 @@ inline std::vector<int> piece_lengths(const std::vector<int>& len, const std::ve
 //   160         0 / +14     -2 / +13    -4 / +12    -6 / +9
 //   200        -5 / +14     -6 / +13    -7 / +12    -7 / +9
 //   400        -6 / +13     -7 / +12    -7 / +12    -7 / +8
+// Over 6896 steps drawn from mixed shapes (50 to 400 MiB by this measure, both
+// tree rules, paged and packed, equal and ragged contexts, bf16 and fp32) its
+// choice is 0.9 % slower in a row than the better of both on average; a model
+// of all the sizes would still be 0.4 %.  What it leaves: 5 % of the one-stream
+// steps over 60 MiB would be 8 % or more faster in a row on two (over half of them
+// with 25 to 75 MiB of logits, or under the sequential rule; nearly all are
+// slower on two when waited for).
 inline bool overlap_pays(int64_t kv_bytes, int64_t logit_bytes) {
   return kv_bytes + logit_bytes + logit_bytes / 5 > (int64_t)165 << 20;
 }
@@ -229,8 +236,8 @@ struct LmhGeometry {
 //    without any.  V = 32000, K = 1024 to 8192: M = 20 0.89-0.82, 95 1.01-0.85,
 //    190 1.02-0.94; V = 9000, M = 20 0.83-0.62, 125 1.01-0.92, 160 1.12-1.07.
 //    Weights that stay in the Infinity Cache between calls (256 MB) favour the
-//    tall tiles' cached loads beyond 64 rows: V = 32000, K = 1024, M = 95 1.07, V
-//    = 16000, K = 4096, M = 125 1.08, 160 1.20;
+//    tall tiles' cached loads beyond 64 rows: V = 32000, K = 1024, M = 95 1.07, K
+//    = 2048, M = 95 1.13, 160 1.02, V = 16000, K = 4096, M = 125 1.08, 160 1.20;
 //  - more rounds, fewer than two for each of the tall tiles': V = 78071, M =
 //    20 0.87-0.84, 95 1.01-0.89, 190 1.07-1.02 (from the cache, K = 2048 on, 95
 //    0.95-0.85, 190 0.98);
